@@ -31,6 +31,37 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// gfx950 issues plain fp32 instructions of two waves of a SIMD side by side (about 2.3
+// cycles each per SIMD), an exponential alone (8 cycles).  Exponentials scattered
+// through a wave's arithmetic keep the waves out of step and nearly nothing pairs: 4.5
+// cycles per instruction on a loop of the chunk aggregates' mix (one exponential in
+// seven).  Issued as a group at raised wave priority, the waves meet behind them and
+// run the rest paired: 3.2 (31.4 -> 22.0 cycles per state and step; the forward's mix,
+// one in five, 24.1 -> 18.7).  In the kernels, with their other work: forward 785 ->
+// 750 us, its aggregates 590 -> 535 (T = 65,536, b = 2, D = 1,536); k_grad 2 % step by
+// step and another 1.5 % with a segment's broadcasts and decays in one group (13.3 ->
+// 12.9 ms at the slice workload).
+// Beginning of a step's transcendental part and its end.
+__device__ __forceinline__ void trans_begin() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+}
+__device__ __forceinline__ void trans_end() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+}
+
+// a[i] = 2^{c[i] x}: the decays of one step
+template <int N>
+__device__ __forceinline__ void decays(const float (&c)[N], float x, float (&a)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) a[i] = c[i] * x;
+    trans_begin();
+#pragma unroll
+    for (int i = 0; i < N; ++i) a[i] = fexp2(a[i]);
+    trans_end();
+}
+
 __device__ __forceinline__ float ldf(const float* p, int64_t i) { return p[i]; }
 __device__ __forceinline__ float ldf(const uint16_t* p, int64_t i) {
     return __uint_as_float(static_cast<uint32_t>(p[i]) << 16);
@@ -323,6 +354,14 @@ struct SRow {
             }
         }
     }
+    // the 16 values as fp32 in scalar registers, here and not at their uses
+    __device__ __forceinline__ void unpack(float (&v)[16]) const {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            v[k] = at(k);
+            asm volatile("" : "+s"(v[k]));
+        }
+    }
     __device__ __forceinline__ float at(int k) const {
         if constexpr (PACKED) return __uint_as_float((k & 1) ? (w[k >> 1] & 0xffff0000u) : (w[k >> 1] << 16));
         else return __uint_as_float(w[k]);
@@ -447,18 +486,24 @@ __global__ __launch_bounds__(64) void k_chunk_aggr(const ScanProblem p) {
     // one step from its raw inputs and its rows of B and C
     auto step = [&](float xr, float pr, float dyr, float zr, const SRow<TI, N16>& cB,
                     const SRow<TI, N16>& cC) __attribute__((always_inline)) {
+        trans_begin();
         const float dl = SP ? softplus_f(pr) : pr;
         if (p.bdelta) xr *= dl;  // input term Delta B x
         float g = 0.f;
         if constexpr (WANT_M) g = GATE ? dyr * zr * sigmoid_f(zr) : dyr;
         sd += static_cast<double>(dl);
+        float av[16], fB[16], fC[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) av[i] = fexp2(cn[i] * dl);
+        cB.unpack(fB);
+        if constexpr (WANT_M) cC.unpack(fC);  // scalar work behind the exponentials
+        trans_end();
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            const float av = fexp2(cn[k] * dl);
-            h[k] = fmaf(av, h[k], cB.at(k) * xr);
+            h[k] = fmaf(av[k], h[k], fB[k] * xr);
             if constexpr (WANT_M) {
-                P[k] *= av;
-                m[k] = fmaf(g * cC.at(k), P[k], m[k]);
+                P[k] *= av[k];
+                m[k] = fmaf(g * fC[k], P[k], m[k]);
             }
         }
     };
@@ -672,12 +717,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                 Cv[0] = c4.x; Cv[1] = c4.y; Cv[2] = c4.z; Cv[3] = c4.w;
             }
             const float g = WANT_M ? quad_bcast(gr, j) : 0.f;
+            float av[4];
+            decays(cn, dl, av);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const float av = fexp2(cn[k] * dl);
-                h[k] = fmaf(av, h[k], Bv[k] * xv);
+                h[k] = fmaf(av[k], h[k], Bv[k] * xv);
                 if constexpr (WANT_M) {
-                    P[k] *= av;
+                    P[k] *= av[k];
                     m[k] = fmaf(g * Cv[k], P[k], m[k]);
                 }
             }
@@ -851,21 +897,28 @@ __global__ __launch_bounds__(64) void k_forward(const ScanProblem p) {
         static_cast<TI*>(p.y) + (rowb + t0) * p.D, 0, static_cast<int>(nl * p.D * sizeof(TI)), 0x00020000);
     auto step = [&](int tl, float xr, float pr, float zr, const SRow<TI, N16>& cB,
                     const SRow<TI, N16>& cC) __attribute__((always_inline)) {
+        trans_begin();
         const float dl = SP ? softplus_f(pr) : pr;
         if (p.bdelta) xr *= dl;  // input term Delta B x
-        float yq[4];
+        if constexpr (GATE) zr *= sigmoid_f(zr);
+        float yq[4], av[16], fB[16], fC[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) av[i] = fexp2(cn[i] * dl);
+        cB.unpack(fB);
+        cC.unpack(fC);
+        trans_end();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float yp = 0.f;
 #pragma unroll
             for (int k = 4 * i; k < 4 * i + 4; ++k) {
-                h[k] = fmaf(fexp2(cn[k] * dl), h[k], cB.at(k) * xr);
-                yp = fmaf(cC.at(k), h[k], yp);
+                h[k] = fmaf(av[k], h[k], fB[k] * xr);
+                yp = fmaf(fC[k], h[k], yp);
             }
             yq[i] = yp;
         }
         float y = (yq[0] + yq[1]) + (yq[2] + yq[3]);
-        if constexpr (GATE) y *= zr * sigmoid_f(zr);
+        if constexpr (GATE) y *= zr;
         if constexpr (sizeof(TI) == 2)
             __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, static_cast<__bf16>(y)), rY, cr.voff,
                                                   tl * cr.rowbytes, 0);
@@ -1003,10 +1056,11 @@ __global__ __launch_bounds__(256) void k_forward_quad(const ScanProblem p) {
                 const float4 c4 = *reinterpret_cast<const float4*>(&bcs[tb + j][16 + 4 * r]);
                 const float Bv[4] = {b4.x, b4.y, b4.z, b4.w};
                 const float Cv[4] = {c4.x, c4.y, c4.z, c4.w};
-                float yp = 0.f;
+                float yp = 0.f, av[4];
+                decays(cn, dl, av);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    h[k] = fmaf(fexp2(cn[k] * dl), h[k], Bv[k] * xv);
+                    h[k] = fmaf(av[k], h[k], Bv[k] * xv);
                     yp = fmaf(Cv[k], h[k], yp);
                 }
                 ypart[j] = yp;
@@ -1582,12 +1636,20 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
             float Bn[4], Cn[4];
             const int brow = RING ? (q & 1) * S : q * S;  // the segment's first staged row
             bc.get(brow, r, Bn, Cn);
+            // the segment's broadcasts and decays in one group (see trans_begin)
+            trans_begin();
 #pragma unroll
             for (int j = 0; j < S; ++j) {
-                const int tl = q * S + j;
-                const float xv = quad_bcast(xs[j >> 2], j & 3);
-                const float dl = quad_bcast(dls[j >> 2], j & 3);
-                const float g = quad_bcast(gs[j >> 2], j & 3);
+                xh[j] = quad_bcast(xs[j >> 2], j & 3);
+                dlh[j] = quad_bcast(dls[j >> 2], j & 3);
+                gh[j] = quad_bcast(gs[j >> 2], j & 3);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) ah[j][k] = fexp2(cn[k] * dlh[j]);
+            }
+            trans_end();
+#pragma unroll
+            for (int j = 0; j < S; ++j) {
+                const float xv = xh[j], g = gh[j];
                 float Bv[4], Cv[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -1598,9 +1660,7 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                 float yp = 0.f;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const float av = fexp2(cn[k] * dl);
-                    ah[j][k] = av;
-                    ahp[j][k] = av * h[k];
+                    ahp[j][k] = ah[j][k] * h[k];
                     h[k] = fmaf(Bv[k], xv, ahp[j][k]);
                     if constexpr (GATE) yp = fmaf(Cv[k], h[k], yp);
                     red[wave][j][r * 4 + k][chs] = g * h[k];
@@ -1609,9 +1669,6 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                     ypart[j & 3] = yp;
                     if ((j & 3) == 3) yk[j >> 2] = quad_sum_transposed(ypart, r);  // y of step 4(j/4) + r
                 }
-                gh[j] = g;
-                dlh[j] = dl;
-                xh[j] = xv;
             }
             if constexpr (GATE) {
 #pragma unroll
@@ -1664,10 +1721,11 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                     } else {
                         ld4<TI, N16>(static_cast<const TI*>(p.C), bb * p.T + ps, r, p.N, pv, Cs);
                     }
-                    const float wf = static_cast<float>(W);
+                    float pw[4];  // P(t, t+tbar)
+                    decays(cn, static_cast<float>(W), pw);
 #pragma unroll
                     for (int k = 0; k < 4; ++k)  // the step t+tbar leaves the window
-                        mb[k] = fmaf(-fexp2(cn[k] * wf), gp * Cs[k], mb[k]);
+                        mb[k] = fmaf(-pw[k], gp * Cs[k], mb[k]);
                     W += static_cast<double>(dlh[j]) - static_cast<double>(dlp);
                 }
                 float dxp = 0.f, ddp = 0.f;
