@@ -13,7 +13,7 @@
 //   k_pairs_pre : Delta (softplus of Delta_pre when asked) and g (the upstream
 //                 gradient through the SiLU gate) per (step, channel), fp32;
 //   k_chunk_aggr, k_carry (scan_kernels.h): the state carried into every chunk;
-//   k_pairs     : one lane per (step i, channel), all pairs (t, i) of the window:
+//   k_pairs     : one lane per (8 steps i, channel, 8 states), all pairs (t, i) of the window:
 //                 the sum over t of lambda^{t,i} for the channel's states, into
 //                 a [b][T][D][16] buffer (pairs of different i are independent);
 //   k_pairs_epi : one lane per channel with its states in registers, the steps
@@ -44,102 +44,154 @@ __global__ __launch_bounds__(256) void k_pairs_pre(const ScanProblem p, float* d
     }
 }
 
-// grid (T, ceil(D/64), b), 64 threads: lane = channel d of step i = blockIdx.x.
+// grid (2 ceil(T/8), ceil(D/64), b), 64 threads: lane = channel, the wave one half of
+// the states (8 of 16) for the steps i0 .. i0+7.
 // mu[((b T + i) D + d) 16 + n] = sum_{t=i}^{min(T, i+W)-1} g_t C_t[n] P(i, t) with
-// P(i, i) = 1 and P(i, t) = P(i, t-1) a_t, built as the running product.
-template <typename TI>
-__global__ __launch_bounds__(kPairLanes) void k_pairs(const ScanProblem p, const float* dlv,
-                                                       const float* gv, float* mu, int64_t W) {
+// P(i, i) = 1 and P(i, t) = P(i, t-1) a_t, built as the running product of every i.
+// The steps i share what depends on t alone: the loads of g_t, Delta_t and C_t, the
+// exponential of a_t and the product g_t C_t are made once for eight pairs, which
+// leaves one multiply and one FMA per pair and state (one step per wave: also an
+// exponential, 8 cycles, and two more multiplies; 8.9 -> 3.1 ms at T = 4,096, b = 2,
+// D = 1,536, W = 256).  Eight steps of eight states hold 128 registers of P and m (two
+// waves per SIMD); four steps of 16 states would share each exponential by four only.
+// The order of every sum and product is that of one step per lane.
+constexpr int kPairSteps = 8;   // steps i per wave
+constexpr int kPairStates = 8;  // states per lane
+
+template <typename TI, bool N16>
+__global__ __launch_bounds__(kPairLanes) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_pairs(
+    const ScanProblem p, const float* dlv, const float* gv, float* mu, int64_t W) {
+    constexpr int IB = kPairSteps, NS = kPairStates;
+    constexpr int PB = sizeof(TI) == 2 ? 4 : 2;  // steps t loaded ahead of their use
+    using Bits = typename RawIn<TI, 1>::Bits;
     const int lane = threadIdx.x;
     const int64_t d = static_cast<int64_t>(blockIdx.y) * kPairLanes + lane;
-    const int64_t i = blockIdx.x, bb = blockIdx.z;
+    const int half = blockIdx.x & 1, n0 = half * NS;
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x >> 1) * IB, bb = blockIdx.z;
     if (d >= p.D) return;
-    const TI* Cp = static_cast<const TI*>(p.C);
-    float cn[16], P[16], m[16];
+    float cn[NS], P[IB][NS], m[IB][NS];
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
-        const bool nv = n < p.N;
-        const float al = nv ? p.A_log[p.ascalar ? d : d * p.N + n] : 0.f;
+    for (int n = 0; n < NS; ++n) {
+        const bool nv = n0 + n < p.N;
+        const float al = nv ? p.A_log[p.ascalar ? d : d * p.N + n0 + n] : 0.f;
         cn[n] = nv ? -__expf(al) * kLog2e : 0.f;
-        P[n] = 1.f;
-        m[n] = 0.f;
+#pragma unroll
+        for (int u = 0; u < IB; ++u) {
+            P[u][n] = 1.f;
+            m[u][n] = 0.f;
+        }
     }
     const int64_t rowb = bb * p.T;
-    const int64_t te = min(p.T, i + W);
-    if (p.N == 16) {
-        // eight steps at a time: the batch's loads (from clamped, valid addresses)
-        // are all issued before its arithmetic; steps past the window and the
-        // decay of step i itself are masked to exact no-ops with bit masks
-        // (g = C = 0 leave m unchanged, Delta = 0 leaves P unchanged)
-        constexpr int PB = 8;
-        for (int64_t tb = i; tb < te; tb += PB) {
-            float gb[PB], db[PB];
-            uint32_t cw[PB][sizeof(TI) == 2 ? 8 : 16];
+    const TI* Cp = static_cast<const TI*>(p.C);
+    const int64_t te = min(p.T, i0 + IB - 1 + W);  // past the last window's end
+    // steps before `lo` or from `hi` on belong to the windows of some of the i only
+    const int64_t lo = i0 + IB, hi = min(p.T, i0 + W);
+    // the next PB steps' g, Delta and raw C (past the end: the last step again, not used)
+    struct Batch {
+        float g[PB], dl[PB];
+        Bits c[N16 ? 1 : PB][NS];
+        uint32_t cw[N16 ? PB : 1][sizeof(TI) * NS / 4];
+    };
+    auto load = [&](int64_t tb, Batch& o) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int64_t tc = min(tb + u, te - 1);
-                const int64_t td = (rowb + tc) * p.D + d;
-                gb[u] = gv[td];
-                db[u] = dlv[td];
-                const uint4* row = reinterpret_cast<const uint4*>(Cp + (rowb + tc) * 16);
+        for (int u = 0; u < PB; ++u) {
+            const int64_t row = rowb + min(tb + u, te - 1);
+            o.g[u] = gv[row * p.D + d];
+            o.dl[u] = dlv[row * p.D + d];
+            if constexpr (N16) {
+                const uint4* src = reinterpret_cast<const uint4*>(Cp + row * 16 + n0);
 #pragma unroll
-                for (int q = 0; q < static_cast<int>(sizeof(TI)); ++q) {  // 16-byte pieces of the row
-                    const uint4 w = row[q];
-                    cw[u][4 * q] = w.x;
-                    cw[u][4 * q + 1] = w.y;
-                    cw[u][4 * q + 2] = w.z;
-                    cw[u][4 * q + 3] = w.w;
+                for (int q = 0; q < static_cast<int>(sizeof(TI)) / 2; ++q) {  // 16-byte pieces
+                    const uint4 w = src[q];
+                    o.cw[u][4 * q] = w.x;
+                    o.cw[u][4 * q + 1] = w.y;
+                    o.cw[u][4 * q + 2] = w.z;
+                    o.cw[u][4 * q + 3] = w.w;
                 }
-            }
-            __builtin_amdgcn_sched_barrier(0);
+            } else {
 #pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int64_t t = tb + u;
-                const uint32_t in = t < te ? 0xffffffffu : 0u;
-                const uint32_t dec = t > i && t < te ? 0xffffffffu : 0u;
-                const float gt = __uint_as_float(__float_as_uint(gb[u]) & in);
-                const float dlt = __uint_as_float(__float_as_uint(db[u]) & dec);
-                float Ct[16];
-#pragma unroll
-                for (int n = 0; n < 16; ++n) {
-                    uint32_t b;
-                    if constexpr (sizeof(TI) == 2) b = (n & 1) ? (cw[u][n >> 1] & 0xffff0000u) : (cw[u][n >> 1] << 16);
-                    else b = cw[u][n];
-                    Ct[n] = __uint_as_float(b & in);
-                }
-#pragma unroll
-                for (int n = 0; n < 16; ++n) P[n] *= fexp2(cn[n] * dlt);
-#pragma unroll
-                for (int n = 0; n < 16; ++n) m[n] = fmaf(gt * Ct[n], P[n], m[n]);
+                for (int n = 0; n < NS; ++n) o.c[u][n] = n0 + n < p.N ? ldbits(Cp, row * p.N + n0 + n) : Bits(0);
             }
         }
-    } else {
-        for (int64_t t = i; t < te; ++t) {
-            const int64_t td = (rowb + t) * p.D + d;
-            const float gt = gv[td];
-            float Ct[16];
-            ld_row16(Cp, rowb + t, p.N, Ct);
-            if (t > i) {
-                const float dlt = dlv[td];
+    };
+    auto cval = [&](const Batch& o, int u, int n) __attribute__((always_inline)) {
+        uint32_t b;
+        if constexpr (!N16) b = sizeof(TI) == 2 ? static_cast<uint32_t>(o.c[u][n]) << 16 : static_cast<uint32_t>(o.c[u][n]);
+        else if constexpr (sizeof(TI) == 2) b = (n & 1) ? (o.cw[u][n >> 1] & 0xffff0000u) : (o.cw[u][n >> 1] << 16);
+        else b = o.cw[u][n];
+        return __uint_as_float(b);
+    };
+    // what step t gives every pair: a_t and g_t C_t
+    float a[NS], gc[NS];
+    auto shared = [&](const Batch& o, int s) __attribute__((always_inline)) {
+        decays(cn, o.dl[s], a);
 #pragma unroll
-                for (int n = 0; n < 16; ++n) P[n] *= fexp2(cn[n] * dlt);
+        for (int n = 0; n < NS; ++n) gc[n] = o.g[s] * cval(o, s, n);
+    };
+    Batch nx;
+    load(i0, nx);
+    int64_t tb = i0;
+    // batches with a step that is not in every window, up to `end`
+    auto edges = [&](int64_t end) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (; tb < end; tb += PB) {
+            const Batch cu = nx;
+            load(tb + PB, nx);
+#pragma unroll
+            for (int s = 0; s < PB; ++s) {
+                shared(cu, s);
+#pragma unroll
+                for (int u = 0; u < IB; ++u) {
+                    // steps past the end and pairs outside the window change nothing, and the
+                    // product starts at distance 1
+                    const int64_t k = tb + s - (i0 + u);
+                    const bool in = k >= 0 && k < W && tb + s < te, dec = in && k > 0;  // wave-uniform
+#pragma unroll
+                    for (int n = 0; n < NS; ++n) {
+                        P[u][n] = dec ? P[u][n] * a[n] : P[u][n];
+                        m[u][n] = in ? fmaf(gc[n], P[u][n], m[u][n]) : m[u][n];
+                    }
+                }
             }
+        }
+    };
+    edges(min(lo, te));
+#pragma unroll 1
+    for (; tb + PB <= hi; tb += PB) {
+        const Batch cu = nx;
+        load(tb + PB, nx);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int n = 0; n < 16; ++n) m[n] = fmaf(gt * Ct[n], P[n], m[n]);
+        for (int s = 0; s < PB; ++s) {
+            shared(cu, s);
+#pragma unroll
+            for (int u = 0; u < IB; ++u)
+#pragma unroll
+                for (int n = 0; n < NS; ++n) {
+                    P[u][n] *= a[n];
+                    m[u][n] = fmaf(gc[n], P[u][n], m[u][n]);
+                }
         }
     }
-    float4* o = reinterpret_cast<float4*>(mu + ((rowb + i) * p.D + d) * 16);
+    edges(te);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = make_float4(m[4 * q], m[4 * q + 1], m[4 * q + 2], m[4 * q + 3]);
+    for (int u = 0; u < IB; ++u) {
+        if (i0 + u >= p.T) break;
+        float4* o = reinterpret_cast<float4*>(mu + ((rowb + i0 + u) * p.D + d) * 16 + n0);
+        o[0] = make_float4(m[u][0], m[u][1], m[u][2], m[u][3]);
+        o[1] = make_float4(m[u][4], m[u][5], m[u][6], m[u][7]);
+    }
 }
 
 // grid (ceil(D/64), nc, b), 64 threads.  hbuf holds the state carried into each
 // chunk on entry and receives the chunk's dA_log partial (dA * wn) on exit, at
-// the same index.
-template <typename TI, bool SP, bool GATE>
+// the same index.  The walk is serial, so a step's inputs are loaded a step ahead and
+// the 32 channel sums are 16-byte LDS reads over all lanes (64 reads by half the lanes,
+// next to the loads: 417 -> 258 us at T = 4,096, b = 2, D = 1,536).
+template <typename TI, bool SP, bool GATE, bool N16>
 __global__ __launch_bounds__(kPairLanes) void k_pairs_epi(const ScanProblem p, const float* dlv,
                                                            const float* gv, const float* mu) {
-    __shared__ float red[kPairLanes][33];
+    __shared__ __attribute__((aligned(16))) float red[32][kPairLanes + 4];  // [dB, dC state][channel]
     const int lane = threadIdx.x;
     const int64_t d = static_cast<int64_t>(blockIdx.x) * kPairLanes + lane;
     const int64_t c = blockIdx.y, bb = blockIdx.z;
@@ -189,36 +241,57 @@ __global__ __launch_bounds__(kPairLanes) void k_pairs_epi(const ScanProblem p, c
     const int64_t bsz = p.nb * p.T * p.N;
     float* pB = p.pB + static_cast<int64_t>(blockIdx.x) * bsz;
     float* pC = p.pC + static_cast<int64_t>(blockIdx.x) * bsz;
-    for (int64_t i = t0; i < t1; ++i) {
+    // step i's inputs, loaded one step ahead (the last step reloads its own)
+    struct In {
+        float dl, g, dy, z, x;
+        float4 lam[4];
+        SRow<TI, N16> B, C;
+    };
+    auto load = [&](int64_t i, In& o) __attribute__((always_inline)) {
         const int64_t td = (rowb + i) * p.D + dd;
-        const float dl = dlv[td], g = gv[td];
-        const float xr = ldf(X, td);
-        const float xs = p.bdelta ? xr * dl : xr;  // the input term is (Delta) B x
-        float Bi[16], Ci[16], lam[16];
-        ld_row16(Bp, rowb + i, p.N, Bi);
-        ld_row16(Cp, rowb + i, p.N, Ci);
+        o.dl = dlv[td];
+        o.g = gv[td];
+        o.x = ldf(X, td);
+        o.dy = GATE ? ldf(DY, td) : 0.f;
+        o.z = GATE ? ldf(Z, td) : 0.f;
         const float4* mi = reinterpret_cast<const float4*>(mu + td * 16);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 v = mi[q];
-            lam[4 * q] = v.x; lam[4 * q + 1] = v.y; lam[4 * q + 2] = v.z; lam[4 * q + 3] = v.w;
-        }
+        for (int q = 0; q < 4; ++q) o.lam[q] = mi[q];
+        o.B.load(Bp, rowb + i, p.N);
+        o.C.load(Cp, rowb + i, p.N);
+    };
+    // lane l adds 32 channels of sum l / 2, lane l ^ 1 the others
+    const int ro = lane >> 1, rh = (lane & 1) * 32;
+    In nx;
+    load(t0, nx);
+    for (int64_t i = t0; i < t1; ++i) {
+        const In cu = nx;
+        load(min(i + 1, t1 - 1), nx);
+        __builtin_amdgcn_sched_barrier(0);
+        const int64_t td = (rowb + i) * p.D + dd;
+        const float dl = cu.dl, g = cu.g, xr = cu.x;
+        const float xs = p.bdelta ? xr * dl : xr;  // the input term is (Delta) B x
+        const float lam[16] = {cu.lam[0].x, cu.lam[0].y, cu.lam[0].z, cu.lam[0].w, cu.lam[1].x, cu.lam[1].y,
+                               cu.lam[1].z, cu.lam[1].w, cu.lam[2].x, cu.lam[2].y, cu.lam[2].z, cu.lam[2].w,
+                               cu.lam[3].x, cu.lam[3].y, cu.lam[3].z, cu.lam[3].w};
         float ah[16], y = 0.f;
+        decays(cn, dl, ah);
 #pragma unroll
         for (int n = 0; n < 16; ++n) {
-            ah[n] = fexp2(cn[n] * dl) * h[n];  // a_i h_{i-1}
-            h[n] = fmaf(Bi[n], xs, ah[n]);
-            y = fmaf(Ci[n], h[n], y);
+            ah[n] *= h[n];  // a_i h_{i-1}
+            h[n] = fmaf(cu.B.at(n), xs, ah[n]);
+            y = fmaf(cu.C.at(n), h[n], y);
         }
         float dxp = 0.f, ddp = 0.f;
+        wave_lds_sync();
 #pragma unroll
         for (int n = 0; n < 16; ++n) {
-            dxp = fmaf(lam[n], Bi[n], dxp);
+            dxp = fmaf(lam[n], cu.B.at(n), dxp);
             const float s = lam[n] * ah[n];
             ddp = fmaf(s, wn[n], ddp);
             dA[n] = fmaf(s, dl, dA[n]);
-            red[lane][n] = dv ? lam[n] * xs : 0.f;      // dB_i[n] over channels
-            red[lane][16 + n] = dv ? g * h[n] : 0.f;    // dC_i[n] over channels
+            red[n][lane] = dv ? lam[n] * xs : 0.f;      // dB_i[n] over channels
+            red[16 + n][lane] = dv ? g * h[n] : 0.f;    // dC_i[n] over channels
         }
         // with the Delta-scaled input, dx' = sum_n lambda B gives dx = dx' Delta and
         // adds dx' x to dDelta
@@ -227,18 +300,23 @@ __global__ __launch_bounds__(kPairLanes) void k_pairs_epi(const ScanProblem p, c
             p.dx[td] = p.bdelta ? dxp * dl : dxp;
             p.ddelta[td] = SP ? dd0 * (1.f - fexp(-dl)) : dd0;  // d softplus / d Delta_pre
             if constexpr (GATE) {
-                const float zv = ldf(Z, td);
-                const float sg = sigmoid_f(zv);
-                p.dz[td] = ldf(DY, td) * sg * (1.f + zv * (1.f - sg)) * y;
+                const float sg = sigmoid_f(cu.z);
+                p.dz[td] = cu.dy * sg * (1.f + cu.z * (1.f - sg)) * y;
             }
         }
-        __syncthreads();
-        if (lane < 32 && (lane & 15) < p.N) {
-            float sum = 0.f;
-            for (int l = 0; l < kPairLanes; ++l) sum += red[l][lane];
-            (lane < 16 ? pB : pC)[(rowb + i) * p.N + (lane & 15)] = sum;
+        wave_lds_sync();
+        float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float4 v = *reinterpret_cast<const float4*>(&red[ro][rh + 4 * q]);
+            s4.x += v.x;
+            s4.y += v.y;
+            s4.z += v.z;
+            s4.w += v.w;
         }
-        __syncthreads();
+        float sum = (s4.x + s4.y) + (s4.z + s4.w);
+        sum += dpp_swap1(sum);
+        if ((lane & 1) == 0 && (ro & 15) < p.N) (ro < 16 ? pB : pC)[(rowb + i) * p.N + (ro & 15)] = sum;
     }
     if (dv)
         for (int n = 0; n < p.N; ++n) p.hbuf[cb + n * p.D] = dA[n] * wn[n];
@@ -266,13 +344,15 @@ hipError_t pairs_impl(const ScanProblem& p, float* dl, float* g, float* mu, int6
     }
     {
         SSMK_TIMED("pairs", s);
-        dim3 gp(static_cast<unsigned>(p.T), cdiv(p.D, kPairLanes), static_cast<unsigned>(p.nb));
-        hipLaunchKernelGGL((k_pairs<TI>), gp, dim3(kPairLanes), 0, s, p, dl, g, mu, W);
+        dim3 gp(2 * cdiv(p.T, kPairSteps), cdiv(p.D, kPairLanes), static_cast<unsigned>(p.nb));
+        if (p.N == 16) hipLaunchKernelGGL((k_pairs<TI, true>), gp, dim3(kPairLanes), 0, s, p, dl, g, mu, W);
+        else hipLaunchKernelGGL((k_pairs<TI, false>), gp, dim3(kPairLanes), 0, s, p, dl, g, mu, W);
     }
     {
         SSMK_TIMED("pairs_epilogue", s);
         dim3 ge(cdiv(p.D, kPairLanes), static_cast<unsigned>(p.nc), static_cast<unsigned>(p.nb));
-        hipLaunchKernelGGL((k_pairs_epi<TI, SP, GATE>), ge, dim3(kPairLanes), 0, s, p, dl, g, mu);
+        if (p.N == 16) hipLaunchKernelGGL((k_pairs_epi<TI, SP, GATE, true>), ge, dim3(kPairLanes), 0, s, p, dl, g, mu);
+        else hipLaunchKernelGGL((k_pairs_epi<TI, SP, GATE, false>), ge, dim3(kPairLanes), 0, s, p, dl, g, mu);
     }
     SSMK_TIMED("reduce", s);
     hipLaunchKernelGGL(k_reduce_bc, dim3(cdiv(p.nb * p.T * p.N, 256)), dim3(256), 0, s, p);
