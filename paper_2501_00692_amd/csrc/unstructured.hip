@@ -33,11 +33,20 @@
 //   k_un_proj  : per step, the two reductions over the P channels that the
 //                sequential passes need: bx_t = B_t x_t and v_t = C_t^T dy_t
 //                (fully parallel, ahead of the chunk passes, so that these walk
-//                only A_t and two 16-vectors per step, loaded a step ahead).
-// Lane layout of a wave: lane l = 16 q + i; i indexes a row of the 16 x 16
-// matrices, q one of four quarters of the reduction (matrix columns 4q..4q+3,
-// or a quarter of the P channels), summed across quarters with two xor
-// shuffles.  Vectors of 16 are kept replicated in all four quarters.
+//                only A_t and two 16-vectors per step).
+// Lane layout of a wave: lane l = 16 q + i; the 16 x 16 matrices are held in the
+// MFMA output layout (component r of lane (q, i): row 4q + r, column i) and the
+// state vectors as such matrices with equal columns (component r: element 4q + r),
+// so that a step's product needs no data movement between lanes (mul_vals).
+// The passes over the steps are chains of dependent products.  What bounded them was
+// the latency of each step's loads, one step ahead, and of the lane exchanges of the
+// vector products; the loads now run 8 to 16 steps ahead (walk) and the vectors go
+// through MFMA.  At b = 8, T = 16,384, P = 64, tbar = 256: k_un_wsuf 187 -> 72 us,
+// k_un_wpre 96 -> 49, k_un_carry 82 -> 43, k_un_aggr 46 -> 39, k_un_madj 42 -> 25; what
+// is left there is the chain itself (a product is 64 cycles of MFMA latency and 128 of
+// the matrix pipe, so passes sharing a launch, or a SIMD, only take turns: measured
+// slower).  k_un_proj (1.16 GB, 254 us) and k_un_grad (2.1 GB, 460 us) run at the
+// rate of a plain copy, 4.6 TB/s.
 #include "internal.h"
 
 namespace ssmk {
@@ -45,11 +54,13 @@ namespace {
 
 constexpr int UN = 16;  // state size
 
-// Sum over the four quarters of the wave (lanes i, i+16, i+32, i+48).
+// Sum over the four quarters of the wave (lanes i, i+16, i+32, i+48), by row swaps: no
+// LDS latency in the passes' chains.
 __device__ __forceinline__ float qsum(float v) {
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const uint32_t s = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(s, s, false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 struct UnArgs {
@@ -75,12 +86,6 @@ struct UnArgs {
     float* y;         // [b][T][16]: y_j = Phi(k, j)^T v_j (truncated mode)
     float* bx;        // [b][T][16]: B_t x_t
 };
-
-// h[4q + r] from the lane that holds it (vectors of 16 are replicated in the
-// four quarters; lane 4q + r of the first quarter has component 4q + r).
-__device__ __forceinline__ float4 quarter_of(float h, int q) {
-    return make_float4(__shfl(h, 4 * q), __shfl(h, 4 * q + 1), __shfl(h, 4 * q + 2), __shfl(h, 4 * q + 3));
-}
 
 // grid (ceil(T / 4), b), 64 threads: four steps per wave, one at a time.
 // bx_t = B_t x_t: instruction j reads rows 4j..4j+3 of B_t (row 4j + g in lanes
@@ -144,14 +149,15 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // lane's own X: the product needs no data movement and its result is again in
 // the output layout.  m4 holds the lane's operand values of M (M[i][4q + kb], a
 // float4 of row i; M[4q + kb][i] for M^T X, see vals_t), loaded ahead by the
-// caller.
-__device__ __forceinline__ f4 mul_vals(const float4 m4, f4 X) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.x, X[0], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.y, X[1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.z, X[2], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.w, X[3], acc, 0, 0, 0);
-    return acc;
+// caller; `add` is added to the product.
+__device__ __forceinline__ f4 mul_vals(const float4 m4, f4 X, f4 add = f4{0.f, 0.f, 0.f, 0.f}) {
+    // two chains of two instructions (each waits for the one before it)
+    f4 z = {0.f, 0.f, 0.f, 0.f};
+    add = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.x, X[0], add, 0, 0, 0);
+    z = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.z, X[2], z, 0, 0, 0);
+    add = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.y, X[1], add, 0, 0, 0);
+    z = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.w, X[3], z, 0, 0, 0);
+    return add + z;
 }
 // Lane 16 q + i's operand values of M^T X.
 __device__ __forceinline__ float4 vals_t(const float* M, int i, int q) {
@@ -163,92 +169,117 @@ __device__ __forceinline__ f4 identity16(int i, int q) {
     return e;
 }
 
+// Sum over the 16 lanes of each quarter of the wave (every lane gets it).
+template <int ROR>
+__device__ __forceinline__ float add_ror(float v) {
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + ROR, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float sum16(float v) { return add_ror<1>(add_ror<2>(add_ror<4>(add_ror<8>(v)))); }
+
+__device__ __forceinline__ f4 vec4(const float4 v) { return f4{v.x, v.y, v.z, v.w}; }
+__device__ __forceinline__ float dot4(f4 a, f4 b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + a[3] * b[3]; }
+__device__ __forceinline__ f4 ld4v(const float* p) { return vec4(*reinterpret_cast<const float4*>(p)); }
+__device__ __forceinline__ void st4v(float* p, f4 v) { *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]); }
+
+// step(k, load(k)) for k = 0 .. n-1 in order, the loads of 8 steps issued together
+// while the 8 steps before them run (two register buffers used alternately; past the
+// end step n-1 is loaded again and not used).
+template <typename Rec, typename Load, typename Step>
+__device__ __forceinline__ void walk(int64_t n, Load load, Step step) {
+    constexpr int U = 8;
+    Rec ra[U], rb[U];
+    auto fill = [&](int64_t k, Rec (&r)[U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = load(min(k + u, n - 1));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto run = [&](int64_t k, const Rec (&r)[U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k + u < n) step(k + u, r[u]);
+    };
+    fill(0, ra);
+    for (int64_t k = 0; k < n; k += 2 * U) {
+        fill(k + U, rb);
+        run(k, ra);
+        if (k + U >= n) break;
+        fill(k + 2 * U, ra);
+        run(k + U, rb);
+    }
+}
+
 // grid (nc, b), 64 threads
 __global__ __launch_bounds__(64) void k_un_aggr(const UnArgs a) {
     const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;
     const int64_t c = blockIdx.x, bb = blockIdx.y;
     const int64_t s0 = c * a.L, s1 = min(s0 + a.L, a.T);
-    // Phi in the MFMA output layout: lane (q, i) holds Phi[4q + r][i], r = 0..3
-    f4 phi = identity16(i, q);
-    float h = 0.f, m = 0.f;  // replicated: lane (q, i) holds h[i], m[i]
-    // step t's A_t[i][4q..4q+3], bx_t[i] and v_t[4q..4q+3], loaded a step ahead
-    // (the last step reloads its own)
     const int64_t r0 = bb * a.T + s0;
-    float4 an = *reinterpret_cast<const float4*>(a.A + r0 * UN * UN + i * UN + 4 * q);
-    float bn = a.bx[r0 * UN + i];
-    float4 vn = *reinterpret_cast<const float4*>(a.v + r0 * UN + 4 * q);
-    for (int64_t t = s0; t < s1; ++t) {
-        const int64_t row = bb * a.T + t;
-        const float4 a4 = an, v4 = vn;
-        const float bxt = bn;
-        const int64_t nx = t + 1 < s1 ? row + 1 : row;
-        an = *reinterpret_cast<const float4*>(a.A + nx * UN * UN + i * UN + 4 * q);
-        bn = a.bx[nx * UN + i];
-        vn = *reinterpret_cast<const float4*>(a.v + nx * UN + 4 * q);
-        // h <- A_t h + B_t x_t
-        const float4 hq = quarter_of(h, q);
-        h = qsum(a4.x * hq.x + a4.y * hq.y + a4.z * hq.z + a4.w * hq.w) + bxt;
-        // Phi <- A_t Phi (operands in registers, see mul_vals)
-        phi = mul_vals(a4, phi);
-        if (!a.trunc) {
+    f4 phi = identity16(i, q);
+    f4 h = {0.f, 0.f, 0.f, 0.f};
+    float m = 0.f;  // lane (q, j): the quarter's share of m[j]
+    struct Rec {
+        float4 A;
+        f4 bx, v;
+    };
+    walk<Rec>(
+        s1 - s0,
+        [&](int64_t k) {
+            const int64_t row = r0 + k;
+            return Rec{*reinterpret_cast<const float4*>(a.A + row * UN * UN + i * UN + 4 * q), ld4v(a.bx + row * UN + 4 * q),
+                       ld4v(a.v + row * UN + 4 * q)};
+        },
+        [&](int64_t, const Rec& r) {
+            h = mul_vals(r.A, h, r.bx);  // h <- A_t h + B_t x_t
+            phi = mul_vals(r.A, phi);    // Phi <- A_t Phi
             // the adjoint aggregate m += Phi_t^T v_t; lane (q, j): sum_r Phi[4q + r][j] v[4q + r]
-            m += qsum(phi[0] * v4.x + phi[1] * v4.y + phi[2] * v4.z + phi[3] * v4.w);
-        }
-    }
+            if (!a.trunc) m += dot4(phi, r.v);
+        });
     const int64_t cb = bb * a.nc + c;
     for (int r = 0; r < 4; ++r) a.phi[cb * UN * UN + (4 * q + r) * UN + i] = phi[r];
-    if (q == 0) {
-        a.hc[cb * UN + i] = h;
-        a.mc[cb * UN + i] = m;
-    }
+    m = qsum(m);
+    if (q == 0) a.mc[cb * UN + i] = m;
+    if (i == 0) st4v(a.hc + cb * UN + 4 * q, h);
 }
 
-// grid (2 b), 64 threads: lanes (q, i) as above; workgroup 2 bb + dir walks
-// sequence bb forwards (dir 0) or backwards (dir 1); each chunk's Phi and
-// aggregate loaded a chunk ahead.
+// grid (2 b), 64 threads: workgroup 2 bb + dir walks the chunks of sequence bb
+// forwards (dir 0) or backwards (dir 1).  Each carry replaces the aggregate it has
+// consumed (which was loaded before).
 __global__ __launch_bounds__(64) void k_un_carry(const UnArgs a) {
     const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;
     const int64_t bb = blockIdx.x >> 1;
-    const int dir = blockIdx.x & 1;
     const int64_t nc = a.nc, c0 = bb * nc;
-    if (dir == 1) {
-        // M_{c-1} = Phi_c^T M_c + mloc_c  (lane (q, j): rows 4q..4q+3 of column j)
-        float M = 0.f;
-        const int64_t cl = c0 + nc - 1;
-        float4 qn = vals_t(a.phi + cl * UN * UN, i, q);
-        float mn = a.mc[cl * UN + i];
-        for (int64_t c = nc - 1; c >= 0; --c) {
-            const int64_t cb = c0 + c;
-            const float4 p4 = qn;
-            const float ml = mn;
-            const int64_t nx = c > 0 ? cb - 1 : cb;
-            qn = vals_t(a.phi + nx * UN * UN, i, q);
-            mn = a.mc[nx * UN + i];
-            const float4 mq = quarter_of(M, q);
-            const float Mn = qsum(p4.x * mq.x + p4.y * mq.y + p4.z * mq.z + p4.w * mq.w) + ml;
-            if (q == 0) a.mc[cb * UN + i] = M;  // the carry from the right into chunk c
-            M = Mn;
-        }
-        if (a.dh0 && q == 0) a.dh0[bb * UN + i] = M;
+    struct Rec {
+        float4 P;
+        f4 loc;
+    };
+    f4 X = {0.f, 0.f, 0.f, 0.f};
+    if (blockIdx.x & 1) {
+        // M_{c-1} = Phi_c^T M_c + mloc_c
+        walk<Rec>(
+            nc,
+            [&](int64_t k) {
+                const int64_t cb = c0 + nc - 1 - k;
+                return Rec{vals_t(a.phi + cb * UN * UN, i, q), ld4v(a.mc + cb * UN + 4 * q)};
+            },
+            [&](int64_t k, const Rec& r) {
+                if (i == 0) st4v(a.mc + (c0 + nc - 1 - k) * UN + 4 * q, X);  // the carry from the right into the chunk
+                X = mul_vals(r.P, X, r.loc);
+            });
+        if (a.dh0 && i == 0) st4v(a.dh0 + bb * UN + 4 * q, X);
         return;
     }
-    float H = a.h0 ? a.h0[bb * UN + i] : 0.f;  // replicated
-    // H_{c+1} = Phi_c H_c + hloc_c  (lane (q, i): columns 4q..4q+3 of row i)
-    float4 pn = *reinterpret_cast<const float4*>(a.phi + c0 * UN * UN + i * UN + 4 * q);
-    float hn = a.hc[c0 * UN + i];
-    for (int64_t c = 0; c < nc; ++c) {
-        const int64_t cb = c0 + c;
-        const float4 p4 = pn;
-        const float hl = hn;
-        const int64_t nx = c + 1 < nc ? cb + 1 : cb;
-        pn = *reinterpret_cast<const float4*>(a.phi + nx * UN * UN + i * UN + 4 * q);
-        hn = a.hc[nx * UN + i];
-        const float4 hq = quarter_of(H, q);
-        const float Hn = qsum(p4.x * hq.x + p4.y * hq.y + p4.z * hq.z + p4.w * hq.w) + hl;
-        if (q == 0) a.hc[cb * UN + i] = H;  // the carry into chunk c (hloc_c was read above)
-        H = Hn;
-    }
-    if (a.h_last && q == 0) a.h_last[bb * UN + i] = H;
+    // H_{c+1} = Phi_c H_c + hloc_c
+    if (a.h0) X = ld4v(a.h0 + bb * UN + 4 * q);
+    walk<Rec>(
+        nc,
+        [&](int64_t k) {
+            const int64_t cb = c0 + k;
+            return Rec{*reinterpret_cast<const float4*>(a.phi + cb * UN * UN + i * UN + 4 * q), ld4v(a.hc + cb * UN + 4 * q)};
+        },
+        [&](int64_t k, const Rec& r) {
+            if (i == 0) st4v(a.hc + (c0 + k) * UN + 4 * q, X);  // the carry into the chunk
+            X = mul_vals(r.P, X, r.loc);
+        });
 }
 
 // grid (blocks - 1, b), 64 threads: block beta >= 1, steps [k, k + tbar) with
@@ -259,32 +290,23 @@ __global__ __launch_bounds__(64) void k_un_wpre(const UnArgs a) {
     const int64_t bb = blockIdx.y;
     const int64_t k = (static_cast<int64_t>(blockIdx.x) + 1) * a.tbar;
     if (k >= a.T) return;
-    const int64_t k1 = min(k + a.tbar, a.T);
-    f4 pre = identity16(i, q);
-    // A_j's operand values and v_j of step j, loaded one step ahead (the last step
-    // reloads its own; A_k is loaded and not used)
     const int64_t r0 = bb * a.T + k;
-    float4 an = *reinterpret_cast<const float4*>(a.A + r0 * UN * UN + i * UN + 4 * q);
-    float4 vn = *reinterpret_cast<const float4*>(a.v + r0 * UN + 4 * q);
-    for (int64_t j = k; j < k1; ++j) {
-        const int64_t row = bb * a.T + j;
-        const float4 ac = an, v4 = vn;
-        const int64_t nx = j + 1 < k1 ? row + 1 : row;
-        an = *reinterpret_cast<const float4*>(a.A + nx * UN * UN + i * UN + 4 * q);
-        vn = *reinterpret_cast<const float4*>(a.v + nx * UN + 4 * q);
-        if (j > k) pre = mul_vals(ac, pre);
-        const float y = qsum(pre[0] * v4.x + pre[1] * v4.y + pre[2] * v4.z + pre[3] * v4.w);
-        if (q == 0) a.y[row * UN + i] = y;
-    }
-}
-
-// Sum over the 16 lanes of each quarter of the wave.
-__device__ __forceinline__ float sum16(float v) {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 8);
-    return v;
+    f4 pre = identity16(i, q);
+    struct Rec {
+        float4 A;
+        f4 v;
+    };
+    walk<Rec>(
+        min(a.tbar, a.T - k),
+        [&](int64_t j) {
+            const int64_t row = r0 + j;  // (A_k is loaded and not used)
+            return Rec{*reinterpret_cast<const float4*>(a.A + row * UN * UN + i * UN + 4 * q), ld4v(a.v + row * UN + 4 * q)};
+        },
+        [&](int64_t j, const Rec& r) {
+            if (j > 0) pre = mul_vals(r.A, pre);
+            const float y = qsum(dot4(pre, r.v));
+            if (q == 0) a.y[(r0 + j) * UN + i] = y;
+        });
 }
 
 // grid (blocks, b), 64 threads: block beta, steps [beta tbar, k) with k =
@@ -294,140 +316,137 @@ __device__ __forceinline__ float sum16(float v) {
 __global__ __launch_bounds__(64) void k_un_wsuf(const UnArgs a) {
     const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;
     const int64_t bb = blockIdx.y;
-    const int64_t k0 = static_cast<int64_t>(blockIdx.x) * a.tbar;
-    const int64_t k = k0 + a.tbar;
+    const int64_t k = (static_cast<int64_t>(blockIdx.x) + 1) * a.tbar;
     if (k >= a.T) return;
-    f4 sm = identity16(i, q);
-    // A_{t+1}'s operand values and y_{t+tbar} of the next step, loaded one step
-    // ahead (clamped to valid rows; a y past the end is not used)
     const int64_t base = bb * a.T;
-    float4 an = vals_t(a.A + (base + k) * UN * UN, i, q);
-    float yv = a.y[(base + min(k - 1 + a.tbar, a.T - 1)) * UN + i];
-    for (int64_t t = k - 1; t >= k0; --t) {
-        const int64_t row = base + t;
-        const float4 ac = an;
-        const float yn = yv;
-        const int64_t tn = t > k0 ? t - 1 : t;
-        an = vals_t(a.A + (base + tn + 1) * UN * UN, i, q);
-        yv = a.y[(base + min(tn + a.tbar, a.T - 1)) * UN + i];
-        sm = mul_vals(ac, sm);
-        if (t + a.tbar >= a.T) continue;  // wave-uniform
-        float w[4];
+    f4 sm = identity16(i, q);
+    struct Rec {
+        float4 A;
+        f4 v;
+        float y;
+    };
+    walk<Rec>(
+        a.tbar,
+        [&](int64_t j) {
+            const int64_t t = k - 1 - j;  // a y past the end is not used
+            return Rec{vals_t(a.A + (base + t + 1) * UN * UN, i, q), ld4v(a.v + (base + t) * UN + 4 * q),
+                       a.y[(base + min(t + a.tbar, a.T - 1)) * UN + i]};
+        },
+        [&](int64_t j, const Rec& r) {
+            const int64_t t = k - 1 - j;
+            sm = mul_vals(r.A, sm);
+            if (t + a.tbar >= a.T) return;  // wave-uniform
+            f4 w;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = sum16(sm[r] * yn);
-        if (i < 4) {
-            const float wr = i == 0 ? w[0] : i == 1 ? w[1] : i == 2 ? w[2] : w[3];
-            a.v[row * UN + 4 * q + i] -= wr;
-        }
-    }
+            for (int c = 0; c < 4; ++c) w[c] = sum16(sm[c] * r.y);
+            if (i == 0) st4v(a.v + (base + t) * UN + 4 * q, r.v - w);
+        });
 }
 
 // grid (nc, b), 64 threads: the chunk's adjoint aggregate of u (v after
 // k_un_wsuf), as k_un_aggr forms it from v in full mode: rho_e = u_e,
 // rho_t = u_t + A_{t+1}^T rho_{t+1}, mloc = A_s^T rho_s.
 __global__ __launch_bounds__(64) void k_un_madj(const UnArgs a) {
-    __shared__ float sr[UN];
     const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;
     const int64_t c = blockIdx.x, bb = blockIdx.y;
     const int64_t s0 = c * a.L, s1 = min(s0 + a.L, a.T);
-    float carry = 0.f;  // A_{t+1}^T rho_{t+1} (replicated)
-    for (int64_t t = s1 - 1; t >= s0; --t) {
-        const int64_t row = bb * a.T + t;
-        const float rho = a.v[row * UN + i] + carry;
-        if (q == 0) sr[i] = rho;
-        __syncthreads();
-        const float* At = a.A + row * UN * UN;
-        float part = 0.f;
-        for (int r = 0; r < 4; ++r) part = fmaf(At[(4 * q + r) * UN + i], sr[4 * q + r], part);
-        carry = qsum(part);
-        __syncthreads();
-    }
-    if (q == 0) a.mc[(bb * a.nc + c) * UN + i] = carry;
+    const int64_t re = bb * a.T + s1 - 1;
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 carry = zero;  // A_{t+1}^T rho_{t+1}
+    struct Rec {
+        float4 A;
+        f4 v;
+    };
+    walk<Rec>(
+        s1 - s0, [&](int64_t j) { return Rec{vals_t(a.A + (re - j) * UN * UN, i, q), ld4v(a.v + (re - j) * UN + 4 * q)}; },
+        [&](int64_t, const Rec& r) { carry = mul_vals(r.A, r.v + carry); });
+    if (i == 0) st4v(a.mc + (bb * a.nc + c) * UN + 4 * q, carry);
 }
 
-// grid (nc, b), 64 threads; LDS holds the chunk's states h_{s-1} .. h_e.
+// grid (nc, b), 256 threads: wave 0 walks the chunk's states h_{s-1} .. h_e into LDS,
+// wave 1 its adjoints (each needs only its own carry); then the four waves write the
+// vjps of the steps, independent of one another, four steps at a time.
+constexpr int kUnGradWaves = 4;
 template <int L>
-__global__ __launch_bounds__(64) void k_un_grad(const UnArgs a) {
-    __shared__ float shs[L + 1][UN];
-    __shared__ float smu[L][UN];
-    const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;
+__global__ __launch_bounds__(64 * kUnGradWaves) void k_un_grad(const UnArgs a) {
+    __shared__ __attribute__((aligned(16))) float shs[L + 1][UN];
+    __shared__ __attribute__((aligned(16))) float smu[L][UN];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
     const int64_t c = blockIdx.x, bb = blockIdx.y;
     const int64_t s0 = c * L, s1 = min(s0 + L, a.T);
     const int64_t cb = bb * a.nc + c;
-    const int64_t P = a.P;
-    // the states h_{s-1} .. h_e into LDS (h in registers, replicated), with step
-    // t's A_t[i][4q..4q+3] and bx_t[i] loaded a step ahead
-    {
-        float h = a.hc[cb * UN + i];
-        if (q == 0) shs[0][i] = h;
-        const int64_t r0 = bb * a.T + s0;
-        float4 an = *reinterpret_cast<const float4*>(a.A + r0 * UN * UN + i * UN + 4 * q);
-        float bn = a.bx[r0 * UN + i];
-        for (int64_t t = s0; t < s1; ++t) {
-            const int64_t row = bb * a.T + t;
-            const float4 a4 = an;
-            const float bxt = bn;
-            const int64_t nx = t + 1 < s1 ? row + 1 : row;
-            an = *reinterpret_cast<const float4*>(a.A + nx * UN * UN + i * UN + 4 * q);
-            bn = a.bx[nx * UN + i];
-            const float4 hq = quarter_of(h, q);
-            h = qsum(a4.x * hq.x + a4.y * hq.y + a4.z * hq.z + a4.w * hq.w) + bxt;
-            if (q == 0) shs[t - s0 + 1][i] = h;
-        }
-    }
-    // the chunk's adjoints, sequential: mu_t = v_t + A_{t+1}^T mu_{t+1} (replicated,
-    // exchanged by shuffles), into LDS; in truncated mode v holds u and the
-    // recurrence gives the windowed adjoint.  v_t and step t's operand values of
-    // A_t^T mu are loaded a step ahead.
-    {
-        float mun = a.mc[cb * UN + i];  // A_{t+1}^T mu_{t+1}
-        const int64_t re = bb * a.T + s1 - 1;
-        float vn = a.v[re * UN + i];
-        float4 an = vals_t(a.A + re * UN * UN, i, q);
-        for (int64_t t = s1 - 1; t >= s0; --t) {
-            const int64_t row = bb * a.T + t;
-            const float vt = vn;
-            const float4 a4 = an;
-            const int64_t nx = t > s0 ? row - 1 : row;
-            vn = a.v[nx * UN + i];
-            an = vals_t(a.A + nx * UN * UN, i, q);
-            const float mu = vt + mun;
-            if (q == 0) smu[t - s0][i] = mu;
-            const float4 mq = quarter_of(mu, q);
-            mun = qsum(a4.x * mq.x + a4.y * mq.y + a4.z * mq.z + a4.w * mq.w);
-        }
+    const int64_t r0 = bb * a.T + s0;
+    const int n = static_cast<int>(s1 - s0);
+    const int P = static_cast<int>(a.P);
+    struct Rec {
+        float4 A;
+        f4 v;
+    };
+    if (wave == 0) {
+        f4 h = ld4v(a.hc + cb * UN + 4 * q);
+        if (i == 0) st4v(&shs[0][4 * q], h);
+        walk<Rec>(
+            n,
+            [&](int64_t k) {
+                const int64_t row = r0 + k;
+                return Rec{*reinterpret_cast<const float4*>(a.A + row * UN * UN + i * UN + 4 * q), ld4v(a.bx + row * UN + 4 * q)};
+            },
+            [&](int64_t k, const Rec& r) {
+                h = mul_vals(r.A, h, r.v);
+                if (i == 0) st4v(&shs[k + 1][4 * q], h);
+            });
+    } else if (wave == 1) {
+        // mu_t = v_t + A_{t+1}^T mu_{t+1}; in truncated mode v holds u and the recurrence
+        // gives the windowed adjoint
+        f4 mun = ld4v(a.mc + cb * UN + 4 * q);  // A_{t+1}^T mu_{t+1}
+        walk<Rec>(
+            n,
+            [&](int64_t k) {
+                const int64_t row = r0 + n - 1 - k;
+                return Rec{vals_t(a.A + row * UN * UN, i, q), ld4v(a.v + row * UN + 4 * q)};
+            },
+            [&](int64_t k, const Rec& r) {
+                const f4 mu = r.v + mun;
+                if (i == 0) st4v(&smu[n - 1 - k][4 * q], mu);
+                mun = mul_vals(r.A, mu);
+            });
     }
     __syncthreads();
-    // the vjps of every step, independent of one another
-    for (int64_t t = s0; t < s1; ++t) {
-        const int64_t row = bb * a.T + t;
-        const int k = static_cast<int>(t - s0);
-        // dA_t[r][4(l%4) .. +3] = mu[r] h_{t-1}[..], r = l / 4
+    // 256 consecutive values of dB_t and dC_t per pass: lane l's four start at row
+    // r, column pb of dB_t (row pc, column rc of dC_t), moved on from pass to pass
+    const int e0 = 4 * lane, er = e0 / P, ep = e0 - er * P, dr = 256 / P, dp = 256 - dr * P, rc = e0 % UN;
+    for (int k = wave; k < n; k += kUnGradWaves) {
+        const int64_t row = r0 + k;
         {
+            // dA_t[r][4(l%4) .. +3] = mu[r] h_{t-1}[..], r = l / 4
             const int r = lane >> 2, c4 = (lane & 3) * 4;
-            const float m = smu[k][r];
-            const float4 hv = make_float4(shs[k][c4] * m, shs[k][c4 + 1] * m, shs[k][c4 + 2] * m,
-                                          shs[k][c4 + 3] * m);
-            *reinterpret_cast<float4*>(a.dA + row * UN * UN + r * UN + c4) = hv;
+            st4v(a.dA + row * UN * UN + e0, ld4v(&shs[k][c4]) * smu[k][r]);
         }
-        // dB_t[r][p] = mu[r] x_t[p]; dC_t[p][r] = dy_t[p] h_t[r]; four values per lane and pass
+        // dB_t[r][p] = mu[r] x_t[p]; dC_t[p][r] = dy_t[p] h_t[r]
         const float* xt = a.x + row * P;
         const float* dyt = a.dy + row * P;
-        for (int64_t e = 4 * lane; e < UN * P; e += 256) {
-            const int64_t r = e / P, p = e % P;
-            const float m = smu[k][r];
-            const float4 x4 = *reinterpret_cast<const float4*>(xt + p);
-            *reinterpret_cast<float4*>(a.dB + row * UN * P + e) = make_float4(m * x4.x, m * x4.y, m * x4.z, m * x4.w);
-            const int64_t pc = e / UN, rc = e % UN;
-            const float g = dyt[pc];
-            *reinterpret_cast<float4*>(a.dC + row * P * UN + e) =
-                make_float4(g * shs[k + 1][rc], g * shs[k + 1][rc + 1], g * shs[k + 1][rc + 2], g * shs[k + 1][rc + 3]);
+        float* dB = a.dB + row * UN * P;
+        float* dC = a.dC + row * UN * P;
+        const f4 hv = ld4v(&shs[k + 1][rc]);
+        int r = er, pb = ep;
+#pragma unroll 4
+        for (int e = e0; e < UN * P; e += 256) {
+            st4v(dB + e, ld4v(xt + pb) * smu[k][r]);
+            st4v(dC + e, hv * dyt[e / UN]);
+            r += dr;
+            pb += dp;
+            if (pb >= P) {
+                pb -= P;
+                ++r;
+            }
         }
         // dx_t[p] = sum_r B_t[r][p] mu[r]
         const float* Bt = a.B + row * UN * P;
-        for (int64_t p = lane; p < P; p += 64) {
+        for (int p = lane; p < P; p += 64) {
             float sx = 0.f;
-            for (int r = 0; r < UN; ++r) sx = fmaf(Bt[r * P + p], smu[k][r], sx);
+#pragma unroll
+            for (int rr = 0; rr < UN; ++rr) sx = fmaf(Bt[rr * P + p], smu[k][rr], sx);
             a.dx[row * P + p] = sx;
         }
     }
@@ -508,11 +527,11 @@ hipError_t launch_unstructured_grad(const UnstructuredProblem& u, void* ws, hipS
     }
     SSMK_TIMED("un_grad", s);
     switch (a.L) {
-        case 16: hipLaunchKernelGGL(k_un_grad<16>, gc, dim3(64), 0, s, a); break;
-        case 32: hipLaunchKernelGGL(k_un_grad<32>, gc, dim3(64), 0, s, a); break;
-        case 64: hipLaunchKernelGGL(k_un_grad<64>, gc, dim3(64), 0, s, a); break;
-        case 128: hipLaunchKernelGGL(k_un_grad<128>, gc, dim3(64), 0, s, a); break;
-        default: hipLaunchKernelGGL(k_un_grad<256>, gc, dim3(64), 0, s, a); break;
+        case 16: hipLaunchKernelGGL(k_un_grad<16>, gc, dim3(64 * kUnGradWaves), 0, s, a); break;
+        case 32: hipLaunchKernelGGL(k_un_grad<32>, gc, dim3(64 * kUnGradWaves), 0, s, a); break;
+        case 64: hipLaunchKernelGGL(k_un_grad<64>, gc, dim3(64 * kUnGradWaves), 0, s, a); break;
+        case 128: hipLaunchKernelGGL(k_un_grad<128>, gc, dim3(64 * kUnGradWaves), 0, s, a); break;
+        default: hipLaunchKernelGGL(k_un_grad<256>, gc, dim3(64 * kUnGradWaves), 0, s, a); break;
     }
     return hipGetLastError();
 }

@@ -56,6 +56,23 @@ def test_unstructured_small_truncated_literal(tbar):
     say("   rel-L2:", " ".join(f"{k}={v:.2e}" for k, v in rep.items()))
 
 
+@pytest.mark.parametrize("T,P,chunk,tbar", [(1, 16, 16, 0), (7, 48, 16, 3), (8, 16, 32, 5), (9, 80, 16, 8), (16, 272, 16, 0),
+                                            (17, 512, 32, 16), (33, 48, 32, 9), (40, 240, 16, 17)])
+def test_unstructured_step_batches(T, P, chunk, tbar):
+    """The passes walk 8 steps per batch and write 256 values of dB and dC at a time:
+    sequences around the batch and widths that do and do not divide 256."""
+    say(f"[unstructured batches] T={T} P={P} chunk={chunk} tbar={tbar}")
+    inp = make_unstructured_inputs(2, T, P, 692205, device="cuda", h0=True)
+    o = _gpu(inp, tbar, chunk, want_dh0=tbar == 0)
+    h = _host(inp)
+    args = [h[k] for k in ("A", "B", "C", "x", "dy")]
+    ref = un_adjoint_sum(*args, tbar=tbar, h0=h["h0"]) if tbar else un_bptt(*args, h["h0"])
+    rep = {}
+    for k in ("dA", "dB", "dC", "dx") + (() if tbar else ("dh0",)):
+        check(k, to_np(o[k]), ref[k], TOL_F32, rep)
+    say("   rel-L2:", " ".join(f"{k}={v:.2e}" for k, v in rep.items()))
+
+
 def test_unstructured_workload_full_every_entry():
     """b = 8, T = 16,384, P = 64, N = 16 (chunks of 64): every output."""
     b, T, P, _ = UN_WORKLOADS["unstructured"]
