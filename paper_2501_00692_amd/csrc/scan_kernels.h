@@ -194,61 +194,6 @@ __device__ __forceinline__ void lane_consts(const float* A_log, int64_t d, int r
     }
 }
 
-// Rows of C at the truncated window's shifted steps (16 states), staged per
-// segment: the S rows x 16 states of a segment are spread over the 64 lanes of a
-// wave, CPL = S/4 consecutive states per lane, and loaded through a raw buffer
-// resource over the rows that exist (rows past it read as zero).  Loading them
-// per step instead, next to their use, left every step waiting for a load: the
-// row's validity is wave-uniform, the compiler branched around the load, and the
-// branch's merge waited for all outstanding memory operations.
-template <typename TI, int S>
-struct ShiftedC {
-    static constexpr int CPL = S / 4;                    // states per lane
-    static constexpr int BYTES = CPL * sizeof(TI);       // 4, 8 or 16
-    using Raw = typename std::conditional<BYTES == 4, uint32_t,
-                typename std::conditional<BYTES == 8, uint32_t __attribute__((ext_vector_type(2))),
-                                          uint32_t __attribute__((ext_vector_type(4)))>::type>::type;
-    static_assert(BYTES == 4 || BYTES == 8 || BYTES == 16, "segment length");
-
-    // raw bits of the rows of segment qs (in-chunk steps qs*S ..) that lane `lane` stages
-    static __device__ __forceinline__ Raw load(__amdgpu_buffer_rsrc_t rs, int qs, int lane) {
-        const int row = qs * S + lane / (16 / CPL), n0 = (lane % (16 / CPL)) * CPL;
-        const int off = (row * 16 + n0) * static_cast<int>(sizeof(TI));
-        if constexpr (BYTES == 4) return __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
-        else if constexpr (BYTES == 8) return __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
-        else return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-    }
-    // fp32 values of the lane's CPL states: into w[j][n / 4][16 + n % 4] (the spare
-    // column of the wave's padded channel-sum rows; states 4r .. 4r+3 of step j end
-    // up at w[j][r][16 .. 19]), or into w[j][n ..] of the wave's own rows of shifted C
-    static __device__ __forceinline__ void stage(const Raw& u, float (&w)[S][16][20], int lane) {
-        const int j = lane / (16 / CPL), n0 = (lane % (16 / CPL)) * CPL;
-        put(u, &w[j][n0 / 4][16 + n0 % 4]);
-    }
-    static __device__ __forceinline__ void stage(const Raw& u, float (&w)[S][16], int lane) {
-        const int j = lane / (16 / CPL), n0 = (lane % (16 / CPL)) * CPL;
-        put(u, &w[j][n0]);
-    }
-    static __device__ __forceinline__ void put(const Raw& u, float* dst) {
-        float v[CPL];
-        if constexpr (sizeof(TI) == 2) {
-#pragma unroll
-            for (int i = 0; i < CPL / 2; ++i) {
-                uint32_t x;
-                if constexpr (BYTES == 4) x = u;
-                else x = u[i];
-                v[2 * i] = __uint_as_float(x << 16);
-                v[2 * i + 1] = __uint_as_float(x & 0xffff0000u);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < CPL; ++i) v[i] = __uint_as_float(u[i]);
-        }
-        if constexpr (CPL == 2) *reinterpret_cast<float2*>(dst) = make_float2(v[0], v[1]);
-        else *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-};
-
 // Uniform loads of the (up to) 16 states of row `row` of a [rows][N] tensor:
 // the same for every lane of the wave.
 template <typename TI>
@@ -297,6 +242,84 @@ __device__ __forceinline__ float fin(uint32_t b, bool v) {
     const float f = sizeof(TI) == 2 ? __uint_as_float(b << 16) : __uint_as_float(b);
     return v ? f : 0.f;
 }
+
+// Rows of C at the truncated window's shifted steps, staged per segment: the S rows x 16 states of a segment are spread over the 64 lanes of a
+// wave, CPL = S/4 consecutive states per lane, and loaded through a raw buffer
+// resource over the rows that exist (rows past it read as zero).  Loading them
+// per step instead, next to their use, left every step waiting for a load: the
+// row's validity is wave-uniform, the compiler branched around the load, and the
+// branch's merge waited for all outstanding memory operations.
+template <typename TI, int S, bool N16>
+struct ShiftedC {
+    static constexpr int CPL = S / 4;                    // states per lane
+    static constexpr int BYTES = CPL * sizeof(TI);       // 4, 8 or 16
+    using Raw = typename std::conditional<BYTES == 4, uint32_t,
+                typename std::conditional<BYTES == 8, uint32_t __attribute__((ext_vector_type(2))),
+                                          uint32_t __attribute__((ext_vector_type(4)))>::type>::type;
+    static_assert(BYTES == 4 || BYTES == 8 || BYTES == 16, "segment length");
+
+    // Fewer than 16 states: the lane's values one by one, from the first shifted row of C
+    // (row x N states; a value that does not exist reads the last that does and is masked)
+    struct Few {
+        uint32_t v[CPL], m[CPL];  // raw bits and masks, applied when they are staged
+    };
+    static __device__ __forceinline__ Few load_few(const TI* C0, int64_t rows, int64_t N, int qs, int lane) {
+        const int64_t row = qs * S + lane / (16 / CPL);
+        const int n0 = (lane % (16 / CPL)) * CPL;
+        Few o;
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+            const bool ok = row < rows && n0 + i < N;
+            o.v[i] = ldbits(C0, ok ? row * N + n0 + i : 0);
+            o.m[i] = ok ? 0xffffffffu : 0u;
+        }
+        return o;
+    }
+    static __device__ __forceinline__ void put(const Few& u, float* dst) {
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) dst[i] = __uint_as_float((sizeof(TI) == 2 ? u.v[i] << 16 : u.v[i]) & u.m[i]);
+    }
+
+    // raw bits of the rows of segment qs (in-chunk steps qs*S ..) that lane `lane` stages
+    static __device__ __forceinline__ Raw load(__amdgpu_buffer_rsrc_t rs, int qs, int lane) {
+        const int row = qs * S + lane / (16 / CPL), n0 = (lane % (16 / CPL)) * CPL;
+        const int off = (row * 16 + n0) * static_cast<int>(sizeof(TI));
+        if constexpr (BYTES == 4) return __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
+        else if constexpr (BYTES == 8) return __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+        else return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+    }
+    // fp32 values of the lane's CPL states: into w[j][n / 4][16 + n % 4] (the spare
+    // column of the wave's padded channel-sum rows; states 4r .. 4r+3 of step j end
+    // up at w[j][r][16 .. 19]), or into w[j][n ..] of the wave's own rows of shifted C
+    template <typename U>
+    static __device__ __forceinline__ void stage(const U& u, float (&w)[S][16][20], int lane) {
+        const int j = lane / (16 / CPL), n0 = (lane % (16 / CPL)) * CPL;
+        put(u, &w[j][n0 / 4][16 + n0 % 4]);
+    }
+    template <typename U>
+    static __device__ __forceinline__ void stage(const U& u, float (&w)[S][16], int lane) {
+        const int j = lane / (16 / CPL), n0 = (lane % (16 / CPL)) * CPL;
+        put(u, &w[j][n0]);
+    }
+    static __device__ __forceinline__ void put(const Raw& u, float* dst) {
+        float v[CPL];
+        if constexpr (sizeof(TI) == 2) {
+#pragma unroll
+            for (int i = 0; i < CPL / 2; ++i) {
+                uint32_t x;
+                if constexpr (BYTES == 4) x = u;
+                else x = u[i];
+                v[2 * i] = __uint_as_float(x << 16);
+                v[2 * i + 1] = __uint_as_float(x & 0xffff0000u);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) v[i] = __uint_as_float(u[i]);
+        }
+        if constexpr (CPL == 2) *reinterpret_cast<float2*>(dst) = make_float2(v[0], v[1]);
+        else *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+};
 
 // Load the raw inputs of the steps j = r + 4*jj of segment [ts, ts+S); lanes whose
 // step (t >= T) or channel is padding load element 0 instead.  `full` also loads
@@ -1267,7 +1290,7 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
     constexpr bool RING = L > 128;
     __shared__ BCStage<TI, RING ? 2 * S : L> bc;
     __shared__ __attribute__((aligned(16))) float red[NW][S][16][RING ? 16 : 20];  // per wave [step][state][channel]
-    __shared__ __attribute__((aligned(16))) float csh[(RING && TRUNC && N16) ? NW : 1][S][16];  // per wave: shifted C
+    __shared__ __attribute__((aligned(16))) float csh[(RING && TRUNC) ? NW : 1][S][16];  // per wave: shifted C
     __shared__ float wsum[4][NW][NP];  // per-wave channel sums: (dC, dB) of a segment, two segments alternating
     __shared__ float acc[L][32];       // chunk totals: dB in columns 0..15, dC in 16..31
     const int tid = threadIdx.x;
@@ -1311,8 +1334,8 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
     const int64_t tile_hi = min(ntile, tile_lo + p.tps);
     const int64_t nit = (tile_hi - tile_lo + NW - 1) / NW;  // the same for every wave
 
-    // truncated mode: the chunk's steps shifted by tbar, and (16 states) a buffer
-    // resource over the rows of C at the shifted steps that exist
+    // truncated mode: the chunk's steps shifted by tbar, and a buffer resource over the
+    // rows of C at the shifted steps that exist (fewer than 16 states: their first row)
     QuadInPtr<TI> qis;
     int64_t lims = 0;
     if constexpr (TRUNC) {
@@ -1320,7 +1343,8 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
         qis.init(p, bb * p.T + min(t0 + p.tbar, p.T - 1));
     }
     const uint32_t D32 = static_cast<uint32_t>(p.D);
-    const int64_t c_rows = (TRUNC && N16) ? max<int64_t>(0, min<int64_t>(L, lims)) : 0;
+    const int64_t c_rows = TRUNC ? max<int64_t>(0, min<int64_t>(L, lims)) : 0;
+    const TI* C0 = static_cast<const TI*>(p.C) + (bb * p.T + min(t0 + p.tbar, p.T - 1)) * p.N;
     const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<TI*>(static_cast<const TI*>(p.C) + (bb * p.T + min(t0 + p.tbar, p.T)) * 16), 0,
         static_cast<int>(c_rows * 16 * static_cast<int64_t>(sizeof(TI))), 0x00020000);
@@ -1422,9 +1446,13 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
         RawIn<TI, SPL> nxs;  // raw inputs at the shifted positions (truncated mode)
         qin.template load<GATE, SPL>(vbi, (NCK - 1) * S, r, nxt);
         if constexpr (TRUNC) qis.template load<GATE, SPL>(D32, d32, (NCK - 1) * S, r, lims, dv, nxs);
-        using SC = ShiftedC<TI, S>;
-        typename SC::Raw nxc{};  // shifted C rows of the next segment (truncated mode, 16 states)
-        if constexpr (TRUNC && N16) nxc = SC::load(rsC, NCK - 1, lane);
+        using SC = ShiftedC<TI, S, N16>;
+        typename std::conditional<N16, typename SC::Raw, typename SC::Few>::type nxc{}, curc{};
+        auto load_c = [&](int qs) __attribute__((always_inline)) {  // shifted C rows of a segment (truncated mode)
+            if constexpr (N16) nxc = SC::load(rsC, qs, lane);
+            else nxc = SC::load_few(C0, c_rows, p.N, qs, lane);
+        };
+        if constexpr (TRUNC) load_c(NCK - 1);
 
         // segment-start states: hseg[q] + (prod of a from the chunk start) H_c, the
         // product being 2^{cn cseg[q]}; loaded one segment ahead
@@ -1451,11 +1479,12 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
             const int64_t e = t0 + L - 1;  // the chunk's last step
             const int64_t pstart = e + tb;
             const int64_t pb = bb * (p.nc + 1) * p.D + d;
-            // Windows shorter than the chunk: the carry a_{e+1} mubar_{e+1} = sum over
-            // s in (e, e+tbar] of g_s C_s P(e, s) is summed directly over those steps
-            // from zero (no difference of full-horizon adjoints at all).  Longer
-            // windows: the full adjoint carry of the chunk holding e+tbar, swept back
-            // to it, is subtracted from the chunk's own carry below.
+            // Windows shorter than p.direct (the chunk, or 128 where the library chose a
+            // shorter chunk): the carry a_{e+1} mubar_{e+1} = sum over s in (e, e+tbar] of
+            // g_s C_s P(e, s) is summed directly over those steps from zero (no difference
+            // of full-horizon adjoints at all).  Longer windows: the full adjoint carry of
+            // the chunk holding e+tbar, swept back to it, is subtracted from the chunk's own
+            // carry below.
             const bool direct = tb < L;
             int64_t cpk = 0, sw_hi = e, sw_lo = e;  // the sweep covers steps (sw_lo, sw_hi]
             if (direct) {
@@ -1590,10 +1619,9 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                 qin.template load<GATE, SPL>(vbi, qn * S, r, nxt);
                 if constexpr (TRUNC) qis.template load<GATE, SPL>(D32, d32, qn * S, r, lims, dv, nxs);
             }
-            typename SC::Raw curc{};
-            if constexpr (TRUNC && N16) {
+            if constexpr (TRUNC) {
                 curc = nxc;
-                nxc = SC::load(rsC, q > 0 ? q - 1 : 0, lane);
+                load_c(q > 0 ? q - 1 : 0);
             }
             // per-channel quantities of the steps this lane prepares
             float dls[SPL], xs[SPL], xr[SPL], gs[SPL], gfs[SPL], dlps[SPL], gps[SPL];
@@ -1681,7 +1709,7 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                 }
             }
             wave_sums(2 * pair);  // dC
-            if constexpr (TRUNC && N16) {
+            if constexpr (TRUNC) {
                 if constexpr (RING) SC::stage(curc, csh[wave], lane);
                 else SC::stage(curc, red[wave], lane);
                 wave_lds_sync();
@@ -1710,17 +1738,11 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
                 for (int k = 0; k < 4; ++k) mb[k] = fmaf(gh[j], Cv[k], Mp[k]);
                 if constexpr (TRUNC) {
-                    const int64_t ps = t0 + tl + p.tbar;
-                    const bool pv = ps < p.T;
                     const float dlp = quad_bcast(dlps[j >> 2], j & 3);
                     const float gp = quad_bcast(gps[j >> 2], j & 3);
                     float Cs[4];
-                    if constexpr (N16) {
-                        const float4 c4 = *reinterpret_cast<const float4*>(RING ? &csh[wave][j][4 * r] : &red[wave][j][r][16]);
-                        Cs[0] = c4.x; Cs[1] = c4.y; Cs[2] = c4.z; Cs[3] = c4.w;
-                    } else {
-                        ld4<TI, N16>(static_cast<const TI*>(p.C), bb * p.T + ps, r, p.N, pv, Cs);
-                    }
+                    const float4 c4 = *reinterpret_cast<const float4*>(RING ? &csh[wave][j][4 * r] : &red[wave][j][r][16]);
+                    Cs[0] = c4.x; Cs[1] = c4.y; Cs[2] = c4.z; Cs[3] = c4.w;
                     float pw[4];  // P(t, t+tbar)
                     decays(cn, static_cast<float>(W), pw);
 #pragma unroll
