@@ -88,8 +88,9 @@ typedef struct {
     int64_t seqlen;   /* T >= 1                                                     */
     int64_t channels; /* D >= 1, at most 2^20 (the paper's P for a diagonal layer)   */
     int64_t dstate;   /* N, 1..16                                                   */
-    int64_t chunk;    /* L, time steps per carry chunk: 0 (default 128), or one of
-                         16, 32, 64, 128, 256.  Results do not depend on it beyond
+    int64_t chunk;    /* L, time steps per carry chunk: 0 (default: 128, or 64 or 32
+                         where a small problem fills the GPU better with them), or one
+                         of 16, 32, 64, 128, 256.  Results do not depend on it beyond
                          rounding.                                                  */
     int32_t in_dtype; /* ssm_dtype of x, delta, B, C, z, dy (and of y)              */
     uint32_t flags;   /* SSM_DELTA_SOFTPLUS | SSM_GATE_SILU | SSM_A_SCALAR | SSM_B_DELTA */

@@ -47,7 +47,7 @@ ssm_status check_desc(const ssm_desc* d, int64_t* L, int64_t* nc) {
         return fail(SSM_ERR_DTYPE, "unknown in_dtype %d", (int)d->in_dtype);
     if (d->flags & ~(SSM_DELTA_SOFTPLUS | SSM_GATE_SILU | SSM_A_SCALAR | SSM_B_DELTA))
         return fail(SSM_ERR_SHAPE, "unknown flag bits 0x%x", (unsigned)d->flags);
-    const int64_t l = d->chunk == 0 ? ssmk::default_chunk() : d->chunk;
+    const int64_t l = d->chunk == 0 ? ssmk::default_chunk(d->batch, d->seqlen, d->channels) : d->chunk;
     if (!ssmk::chunk_supported(l))
         return fail(SSM_ERR_UNSUPPORTED, "chunk %lld not in {16, 32, 64, 128, 256}", (long long)d->chunk);
     const int64_t n = (d->seqlen + l - 1) / l;
@@ -100,6 +100,8 @@ ssmk::ScanProblem make_problem(const ssm_desc* d, int64_t L, int64_t nc) {
     p.N = d->dstate;
     p.L = L;
     p.nc = nc;
+    // a chunk the library chose below 128 keeps the accuracy of 128 for short windows
+    p.direct = d->chunk == 0 && L < ssmk::kDefaultChunk ? ssmk::kDefaultChunk : L;
     p.bf16 = d->in_dtype == SSM_BF16;
     p.softplus = (d->flags & SSM_DELTA_SOFTPLUS) != 0;
     p.gate = (d->flags & SSM_GATE_SILU) != 0;

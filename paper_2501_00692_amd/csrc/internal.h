@@ -42,6 +42,7 @@ struct ScanProblem {
     bool ascalar;    // one decay rate per channel: A_log, dA_log are [D]
     bool bdelta;     // input term Delta * B * x
     int64_t tbar;
+    int64_t direct;  // windows below this sum their entry into a chunk directly (k_grad)
     int nsplit;      // channel splits of the fused kernel (dB/dC partials when > 1)
     int tps;         // 16-channel tiles per split (a multiple of kGradWaves unless one split)
     int nslice;      // slices of the dA_log reduction
@@ -97,7 +98,8 @@ struct ScanWorkspace {
         total;
 };
 
-int64_t default_chunk();
+constexpr int64_t kDefaultChunk = 128;
+int64_t default_chunk(int64_t nb, int64_t T, int64_t D);
 // Segment length of the fused gradient kernel for chunk length L.
 inline int grad_segment(int64_t) { return 8; }
 inline int64_t padded_channels(int64_t D) { return (D + 63) / 64 * 64; }

@@ -23,7 +23,22 @@ size_t align_up(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 
 }  // namespace
 
-int64_t default_chunk() { return 128; }
+// Shorter chunks than 128 where 128 would leave most of the GPU idle: more workgroups,
+// each with a shorter walk, against a longer chain of chunk carries.  A workgroup takes
+// a chunk and at least 64 channels, two per CU run at a time.  32 steps while the grid
+// then still fits one round and the carry chain (T / 32) is at most 64; 64 steps while
+// that holds for them with a chain of at most 128.  Measured (full gradient, fp32, us at
+// 128 / 64 / 32 / 16): b T D = 1 256 64: 64 40 29 29; 1 1024 1024: 67 46 41 54;
+// 1 4096 512: 76 65 79 106; past the lines 2 2048 256 (256 groups at 64): 69 52 53 73,
+// 1 4096 1024: 88 92 107 138, 1 16384 64: 91 95 121 203.  The workspace stays below
+// 32 MiB wherever the chunk is shortened.
+int64_t default_chunk(int64_t nb, int64_t T, int64_t D) {
+    for (int64_t L = 32; L < kDefaultChunk; L *= 2) {
+        const int64_t nc = (T + L - 1) / L;
+        if (nc <= 2 * L && nb <= 512 && nb * nc * ((D + 63) / 64) <= 512) return L;
+    }
+    return kDefaultChunk;
+}
 
 bool chunk_supported(int64_t L) { return L == 16 || L == 32 || L == 64 || L == 128 || L == 256; }
 

@@ -1485,7 +1485,7 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
             // of full-horizon adjoints at all).  Longer windows: the full adjoint carry of
             // the chunk holding e+tbar, swept back to it, is subtracted from the chunk's own
             // carry below.
-            const bool direct = tb < L;
+            const bool direct = tb < p.direct;
             int64_t cpk = 0, sw_hi = e, sw_lo = e;  // the sweep covers steps (sw_lo, sw_hi]
             if (direct) {
                 sw_hi = pstart;

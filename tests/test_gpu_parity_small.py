@@ -324,3 +324,23 @@ def test_layer_grad_optional_outputs(tbar):
     for k in ("dW_in", "dW_x", "dA_log"):
         check(k, to_np(none[k]), ref[k], TOL_BF16, rep)
     say("   rel-L2:", " ".join(f"{k}={v:.2e}" for k, v in rep.items()))
+
+
+@pytest.mark.parametrize("N,bf16", [(16, False), (16, True), (13, False), (6, True)])
+@pytest.mark.parametrize("b,T,D,tbar", [(1, 1, 3, 0), (2, 31, 67, 30), (1, 33, 64, 32), (3, 130, 40, 33), (1, 300, 130, 64),
+                                        (2, 500, 64, 100), (1, 700, 16, 127), (1, 700, 16, 128), (1, 1000, 24, 129),
+                                        (1, 2048, 16, 0), (1, 2100, 16, 50), (1, 2049, 16, 1000)])
+def test_default_chunk(b, T, D, tbar, N, bf16):
+    """The chunk the library chooses (32 up to 2,048 steps on these narrow problems, 64
+    above), slow decays, windows around it and around 128 (up to there a window's entry
+    into a chunk is summed directly); fewer than 16 states stage the window-shifted rows
+    of C value by value."""
+    w = Workload("default_chunk", b, T, D, N, D, 0, True, bf16, 692031, delta_scale=1.0)
+    say(f"[default chunk] b={b} T={T} D={D} N={N} tbar={tbar} bf16={bf16}")
+    inp = _inputs(w, h0=True)
+    for k in ("W_x", "W_in", "u"):
+        inp.pop(k)
+    inp["delta"] = (inp["delta"].float() - 4.0).to(inp["delta"].dtype)  # softplus about 0.02: slow decay
+    full = tbar <= 0 or tbar >= T
+    g = _gpu_grad(inp, w, tbar, 0, want_dh0=full)
+    _compare(g, _oracle_grad(inp, w, tbar, want_dh0=full), TOL_SCAN_BF16 if bf16 else TOL_F32, True, dh0=full)
