@@ -21,11 +21,11 @@
 // outside the matrix (rows, columns, or the reduction tail) read as zero through
 // the buffer range check.  Workgroup: 512 threads = 4x2 waves, two per SIMD;
 // a wave owns a 64 x (BN/2) block of 32x32 MFMA tiles; tile 256 x BN with BN 128
-// or 192.  256 x 256 tiles (dW, and dX with a plain epilogue) run on a kernel of
-// their own (k_gemm4): 256 threads, one wave per SIMD owning a 128 x 128 block
-// with its accumulators in the AGPRs, a five-stage ring (160 KB of LDS), one
-// barrier per step and the MFMAs interleaved one by one with the fragment reads
-// and stage loads.
+// or 192.  256 x 256 tiles run on kernels of their own (k_gemm4 for dW, k_gemm_nt for
+// dX with a plain epilogue): 256 threads, one wave per SIMD owning a 128 x 128 block
+// with its accumulators in the AGPRs and the MFMAs interleaved one by one with the
+// fragment reads and stage loads; dW in a five-stage ring (160 KB of LDS) with one
+// barrier per step, dX in two stages of 64 steps (128 KB).
 // Output tiles and reduction splits are assigned so that each XCD runs one
 // contiguous run of (split, tile) (consecutive workgroups go to different XCDs),
 // tiles ordered in groups of four row blocks, so that the tiles one XCD runs at
@@ -630,67 +630,9 @@ struct ColMajorOps4 {
     }
 };
 
-// The dX form (operands contiguous along the reduction) on the four-wave
-// kernel: the LDS layout of RowMajorOps (64-byte rows of 32 steps, 16-byte
-// blocks XOR-swizzled by (row >> 2) & 3), 256 rows of each operand per stage,
-// four wave loads of A and four of B per wave and stage; each wave reads the
-// 16-byte fragments of its 128 rows of A and 128 rows of B.
-struct RowMajorOps4 {
-    __amdgpu_buffer_rsrc_t ra, rb;
-    uint32_t oa[4], ob[4];
-    int ka[4], kb[4];
-    int64_t k_hi;
-    int offa[2][4], offb[2][4];  // fragment offsets (elements) per sub-step
-
-    __device__ __forceinline__ void init(const GemmArgs& g, int64_t r0, int64_t c0, int64_t khi, int wave,
-                                         int lane, int wr, int wc) {
-        k_hi = khi;
-        // resources over the tile's rows: rows past the matrix read as zero
-        ra = rsrc_uniform(g.A + r0 * g.lda, min<int64_t>(BM, g.R - r0) * g.lda * 2);
-        rb = rsrc_uniform(g.B + c0 * g.ldb, min<int64_t>(256, g.Cc - c0) * g.ldb * 2);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = (wave + 4 * i) * 16 + (lane >> 2);
-            ka[i] = kb[i] = ((lane & 3) ^ RowMajorOps<128>::swz(row)) * 8;
-            oa[i] = static_cast<uint32_t>((row * g.lda + ka[i]) * 2);
-            ob[i] = static_cast<uint32_t>((row * g.ldb + kb[i]) * 2);
-        }
-        const int li = lane & 31, hk = lane >> 5;
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int ra_ = wr + i * 32 + li, rb_ = wc + i * 32 + li;
-                offa[ks][i] = ra_ * BK + (((ks * 2 + hk) ^ RowMajorOps<128>::swz(ra_)) * 8);
-                offb[ks][i] = rb_ * BK + (((ks * 2 + hk) ^ RowMajorOps<128>::swz(rb_)) * 8);
-            }
-    }
-    // pieces past the reduction range read out of range (zero)
-    __device__ __forceinline__ uint32_t off(uint32_t o0, int kq, int64_t k) const {
-        return k + kq < k_hi ? o0 + static_cast<uint32_t>(k * 2) : kOutOfRange;
-    }
-    template <int S>
-    __device__ __forceinline__ void issue(Stage<S>, int64_t k, int wave) const {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) load_lds16(ra, off(oa[i], ka[i], k), stage_a<S>() + (wave + 4 * i) * 512);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) load_lds16(rb, off(ob[i], kb[i], k), stage_b<S>() + (wave + 4 * i) * 512);
-    }
-    template <int S>
-    __device__ __forceinline__ void read(Stage<S>, int ks, bf16x8 (&a)[4], bf16x8 (&b)[4]) const {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            a[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(stage_a<S>() + offa[ks][i]));
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            b[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(stage_b<S>() + offb[ks][j]));
-    }
-};
-
-// Four waves, one per SIMD, each owning a 128 x 128 block of a 256 x 256 output
-// tile: TR selects the dW form (ColMajorOps4) or the dX form (RowMajorOps4, plain
-// epilogues only: no addend, and the fp32 result or its bf16 copy, not both).
-template <bool TR, int NST>
+// The dW form on four waves, one per SIMD, each owning a 128 x 128 block of a 256 x 256
+// output tile.
+template <int NST>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm4(const GemmLaunch gl) {
     constexpr int MI = 4, NJ = 4, BN = 256;
     static_assert(NST == 4 || NST == 5, "stages");
@@ -719,7 +661,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int wc = (wave & 1) * 128;
     const int64_t nsteps = k_hi > k_lo ? (k_hi - k_lo + BK - 1) / BK : 0;
 
-    std::conditional_t<TR, ColMajorOps4, RowMajorOps4> ops;
+    ColMajorOps4 ops;
     ops.init(g, r0, c0, k_hi, wave, lane, wr, wc);
     f32x16 acc[MI][NJ];
 #pragma unroll
@@ -823,25 +765,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 
     float* dst = g.C + (g.direct ? 0 : static_cast<int64_t>(split) * g.R * g.Cc);
+    const int64_t ldc = g.direct ? g.ldc : g.Cc;
     const bool accum = g.direct && g.accum;
     const bool full = r0 + BM <= g.R && c0 + BN <= g.Cc;
-    const int64_t ldc = g.direct ? g.ldc : g.Cc;
     auto store = [&](auto Ft, auto At) __attribute__((always_inline)) {
         store_tile<false, decltype(At)::value, true, false, decltype(Ft)::value>(
             acc, dst, ldc, nullptr, 0, nullptr, 0, g.R, g.Cc, r0 + wr, c0 + wc, lane);
     };
-    if constexpr (!TR) {
-        // the dX form's other plain epilogue: only the bf16 copy (no fp32 result)
-        if (g.direct && g.out16) {
-            if (full)
-                store_tile<false, false, false, true, true>(acc, nullptr, 0, nullptr, 0, g.out16, g.ld16, g.R, g.Cc,
-                                                            r0 + wr, c0 + wc, lane);
-            else
-                store_tile<false, false, false, true, false>(acc, nullptr, 0, nullptr, 0, g.out16, g.ld16, g.R, g.Cc,
-                                                             r0 + wr, c0 + wc, lane);
-            return;
-        }
-    }
     if (full) {
         if (accum) store(std::true_type{}, std::true_type{});
         else store(std::true_type{}, std::false_type{});
@@ -849,6 +779,222 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (accum) store(std::false_type{}, std::true_type{});
         else store(std::false_type{}, std::false_type{});
     }
+}
+
+// Epilogue of a wave's 128 x 128 block (4 x 4 MFMA tiles) at (row0, col0) of the 256 x
+// 256 tile at (r0, c0), through a buffer resource over the tile's rows that exist:
+// columns past the output take an offset past every range, so the block's last rows and
+// columns need no branches (with a branch per element on edge tiles, accumulators spilled:
+// 8191 x 1528 x 1560, one round of tiles, 61 us against 51).  ACC: C += result; O16: the
+// result as bf16 into o16 instead.
+template <bool ACC, bool O16>
+__device__ __forceinline__ void store_block(const f32x16 (&acc)[4][4], float* dst, int64_t ldc, uint16_t* o16, int64_t ld16,
+                                            int64_t R, int64_t Cc, int64_t r0, int64_t c0, int row0, int col0, int lane) {
+    constexpr int EL = O16 ? 2 : 4;
+    const int64_t ld = O16 ? ld16 : ldc;
+    const char* base = O16 ? reinterpret_cast<const char*>(o16) : reinterpret_cast<const char*>(dst);
+    const __amdgpu_buffer_rsrc_t rs = rsrc_uniform(reinterpret_cast<const uint16_t*>(base + (r0 * ld + c0) * EL),
+                                                   min<int64_t>(BM, R - r0) * ld * EL);
+    const uint32_t rb = static_cast<uint32_t>(ld * EL);  // bytes per row; a tile's offsets fit 31 bits (ld <= 2^20)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int col = col0 + j * 32 + (lane & 31);
+        const bool in = c0 + col < Cc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t o[16];
+            float e[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const uint32_t row = row0 + i * 32 + 4 * (lane >> 5) + 8 * (v >> 2) + (v & 3);
+                o[v] = in ? row * rb + static_cast<uint32_t>(col * EL) : kOutOfRange;
+                if constexpr (ACC) e[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o[v], 0, 0));
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                float val = acc[i][j][v];
+                if constexpr (ACC) val += e[v];
+                if constexpr (O16) __builtin_amdgcn_raw_buffer_store_b16(f2bf(val), rs, o[v], 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), rs, o[v], 0, 0);
+            }
+        }
+    }
+}
+
+// The dX form on 256 x 256 tiles: four waves, one per SIMD, each owning a 128 x 128
+// block (4 x 4 MFMA tiles, 256 accumulators in the AGPRs), plain epilogues only (no
+// addend, and the fp32 result or its bf16 copy, not both).  Stages of 64 reduction
+// steps, two in LDS (128 KB): a stage row is 128 bytes, one whole cache line, where
+// stages of 32 steps fetched half a line per row and were bound by the load addressing
+// (texture addresser busy 81 % of the time, MFMA 54 %).  The 16-byte blocks of a row
+// are XOR-swizzled by (row >> 1) & 7, which keeps the fragment reads (16 lanes of
+// consecutive rows at a time over 64 banks) free of conflicts; a 1 KB wave load fills 8
+// rows, lane l supplying row l / 8's logical block (l % 8) ^ swizzle.
+// A stage is four sub-steps of 16 MFMAs; the fragments of a sub-step are read during
+// the one before.  The stage's last fragments are in registers after its third
+// sub-step: there the waves meet (their loads of the next stage landed), and the loads
+// two stages ahead go into the slot just read, A's during the fourth sub-step and B's
+// during the next stage's first.  Measured against 32-step stages in a ring of five (M x K
+// x Nout): 32,768 x 2,048 x 32,000 3.63 -> 3.19 ms (1.18 -> 1.34 PFLOP/s), 262,144 x
+// 4,096 x 4,128 8.29 -> 7.86 ms, 8,192 x 3,072 x 1,536 bf16 out (192 columns on eight
+// waves before) 91.6 -> 87.5 us.
+constexpr int BK2 = 64;
+__shared__ __attribute__((aligned(1024))) uint16_t nA0[BM * BK2];
+__shared__ __attribute__((aligned(1024))) uint16_t nA1[BM * BK2];
+__shared__ __attribute__((aligned(1024))) uint16_t nB0[256 * BK2];
+__shared__ __attribute__((aligned(1024))) uint16_t nB1[256 * BK2];
+
+struct NtOps {
+    __amdgpu_buffer_rsrc_t ra, rb;
+    uint32_t oa, ob, sa, sb;  // the lane's byte offset in the first load's rows; bytes per 32 rows
+    int kq;                   // the lane's first reduction step in a stage
+    int64_t k_hi;
+    int fa[4], fb[4];  // fragment offsets (elements) per sub-step; row block i is 32 i rows further
+
+    __device__ __forceinline__ void init(const GemmArgs& g, int64_t r0, int64_t c0, int64_t khi, int wave, int lane,
+                                         int wr, int wc) {
+        k_hi = khi;
+        // resources over the tile's rows: rows past the matrix read as zero
+        ra = rsrc_uniform(g.A + r0 * g.lda, min<int64_t>(BM, g.R - r0) * g.lda * 2);
+        rb = rsrc_uniform(g.B + c0 * g.ldb, min<int64_t>(256, g.Cc - c0) * g.ldb * 2);
+        const int row = wave * 8 + (lane >> 3);  // load i: 32 i rows further (the same swizzle)
+        kq = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+        oa = static_cast<uint32_t>((row * g.lda + kq) * 2);
+        ob = static_cast<uint32_t>((row * g.ldb + kq) * 2);
+        sa = static_cast<uint32_t>(32 * g.lda * 2);
+        sb = static_cast<uint32_t>(32 * g.ldb * 2);
+        const int li = lane & 31, hk = lane >> 5;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int rA = wr + li, rB = wc + li;
+            fa[ks] = rA * BK2 + (((ks * 2 + hk) ^ ((rA >> 1) & 7)) * 8);
+            fb[ks] = rB * BK2 + (((ks * 2 + hk) ^ ((rB >> 1) & 7)) * 8);
+        }
+    }
+    // pieces past the reduction range read out of range (zero)
+    __device__ __forceinline__ void issue_a(uint16_t* dst, int64_t k, int wave) const {
+        const uint32_t o = oa + static_cast<uint32_t>(k * 2);
+        const bool in = k + kq < k_hi;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) load_lds16(ra, in ? o + i * sa : kOutOfRange, dst + (wave + 4 * i) * 512);
+    }
+    __device__ __forceinline__ void issue_b(uint16_t* dst, int64_t k, int wave) const {
+        const uint32_t o = ob + static_cast<uint32_t>(k * 2);
+        const bool in = k + kq < k_hi;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) load_lds16(rb, in ? o + i * sb : kOutOfRange, dst + (wave + 4 * i) * 512);
+    }
+    static __device__ __forceinline__ void read(const uint16_t* A, const uint16_t* B, int oA, int oB, bf16x8 (&a)[4],
+                                                bf16x8 (&b)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            a[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(A + oA + i * 32 * BK2));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            b[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(B + oB + j * 32 * BK2));
+    }
+};
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_nt(const GemmLaunch gl) {
+    constexpr int MI = 4, NJ = 4;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // tile and split of this workgroup: the XCD-contiguous map and grouped tile order of k_gemm
+    const int nwg = static_cast<int>(gridDim.x);
+    const int lin = static_cast<int>(blockIdx.x);
+    const int xq = nwg / kXcds, xr = nwg % kXcds, xcd = lin % kXcds;
+    const int logical = (xcd < xr ? xcd * (xq + 1) : xr * (xq + 1) + (xcd - xr) * xq) + lin / kXcds;
+    const int tile = logical % gl.tiles, split = logical / gl.tiles;
+    const GemmArgs g = gl.p[0];
+    const int ncb = gl.cb[0], nrb = gl.tiles / ncb;
+    const int grp = tile / (kGroupRows * ncb), first = grp * kGroupRows;
+    const int gh = min(kGroupRows, nrb - first), within = tile - grp * kGroupRows * ncb;
+    const int64_t r0 = static_cast<int64_t>(first + within % gh) * BM;
+    const int64_t c0 = static_cast<int64_t>(within / gh) * 256;
+    const int64_t k_lo = static_cast<int64_t>(split) * g.kper;
+    const int64_t k_hi = min(g.Kr, k_lo + g.kper);
+    const int wr = (wave >> 1) * 128, wc = (wave & 1) * 128;
+    const int64_t n = k_hi > k_lo ? (k_hi - k_lo + BK2 - 1) / BK2 : 0;  // stages
+
+    NtOps ops;
+    ops.init(g, r0, c0, k_hi, wave, lane, wr, wc);
+    f32x16 acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    typedef bf16x8 FA[MI];
+    typedef bf16x8 FB[NJ];
+    auto mm = [&](const FA& a, const FB& b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    };
+    // the MFMAs of a sub-step with the 8 fragment reads (and 8 stage loads) between them
+    auto interleave = [&](auto Loads) __attribute__((always_inline)) {
+        constexpr bool L = decltype(Loads)::value;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // one MFMA
+            if (L) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // one stage load
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);         // one fragment read
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    FA a0, a1;
+    FB b0, b1;
+    // one stage from slot (A, B), its sub-step 0 in (a0, b0); (A2, B2) is the other slot.
+    // Loads past the last stage read out of range and land in a slot nobody reads.
+    auto stage = [&](uint16_t* A, uint16_t* B, uint16_t* A2, uint16_t* B2, int64_t t) __attribute__((always_inline)) {
+        ops.issue_b(B2, k_lo + (t + 1) * BK2, wave);
+        NtOps::read(A, B, ops.fa[1], ops.fb[1], a1, b1);
+        mm(a0, b0);
+        interleave(std::true_type{});
+        NtOps::read(A, B, ops.fa[2], ops.fb[2], a0, b0);
+        mm(a1, b1);
+        interleave(std::false_type{});
+        NtOps::read(A, B, ops.fa[3], ops.fb[3], a1, b1);
+        mm(a0, b0);
+        interleave(std::false_type{});
+        // this wave's loads of stage t + 1 have landed and its reads of stage t are done
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+        ring_barrier();
+        ops.issue_a(A, k_lo + (t + 2) * BK2, wave);
+        NtOps::read(A2, B2, ops.fa[0], ops.fb[0], a0, b0);
+        mm(a1, b1);
+        interleave(std::true_type{});
+    };
+    if (n > 0) {
+        ops.issue_a(nA0, k_lo, wave);
+        ops.issue_b(nB0, k_lo, wave);
+        ops.issue_a(nA1, k_lo + BK2, wave);
+        wait_vm<8>();  // stage 0
+        ring_barrier();
+        NtOps::read(nA0, nB0, ops.fa[0], ops.fb[0], a0, b0);
+        int64_t t = 0;
+        for (; t + 4 <= n; t += 4) {
+            stage(nA0, nB0, nA1, nB1, t);
+            stage(nA1, nB1, nA0, nB0, t + 1);
+            stage(nA0, nB0, nA1, nB1, t + 2);
+            stage(nA1, nB1, nA0, nB0, t + 3);
+        }
+        if (t < n) stage(nA0, nB0, nA1, nB1, t);
+        if (t + 1 < n) stage(nA1, nB1, nA0, nB0, t + 1);
+        if (t + 2 < n) stage(nA0, nB0, nA1, nB1, t + 2);
+        wait_vm<0>();  // no load lands in LDS after the workgroup has given it back
+    }
+
+    float* dst = g.C + (g.direct ? 0 : static_cast<int64_t>(split) * g.R * g.Cc);
+    const int64_t ldc = g.direct ? g.ldc : g.Cc;
+    if (g.direct && g.out16) store_block<false, true>(acc, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0, c0, wr, wc, lane);
+    else if (g.direct && g.accum) store_block<true, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
+    else store_block<false, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
 }
 
 // Second stage of a split GEMM: result = sum over splits (in split order) +
@@ -925,9 +1071,9 @@ constexpr int64_t kMaxWgs = (int64_t(1) << 23) - 1;
 
 // Output-tile width and reduction splits for the outputs R_q x Cc_q of one launch
 // (one or two products) with reduction Kr, from a simple time model: rounds of 256
-// workgroups x the time of one workgroup's share (per 32-step stage at full
-// load, measured: 0.57 us for 128 columns, 0.80 for 192, 0.84 for 256 on the
-// four-wave kernel), plus the
+// workgroups x the time of one workgroup's share (per 32 steps at full load,
+// measured: 0.57 us for 128 columns, 0.80 for 192; 256 on the four-wave kernels:
+// `wide_us`, 0.84 for dW, 0.70 for dX), plus the
 // HBM time of writing and re-reading the split partials (4 TB/s).  256-column
 // tiles (`wide`) for dW, and for dX when its epilogue is plain (no addend, and
 // either the fp32 result or its bf16 copy: the four-wave kernel's registers hold
@@ -937,11 +1083,11 @@ struct Plan {
     int splits;
 };
 
-Plan plan_gemm(int np, const int64_t* R, const int64_t* Cc, int64_t Kr, bool allow_split, bool wide) {
+Plan plan_gemm(int np, const int64_t* R, const int64_t* Cc, int64_t Kr, bool allow_split, bool wide, double wide_us) {
     Plan best{192, 1};
     double best_us = 1e300;
     const int bns[3] = {192, 128, 256};
-    const double step_us[3] = {0.80, 0.57, 0.84};
+    const double step_us[3] = {0.80, 0.57, wide_us};
     double out = 0.0;  // output elements of all products
     for (int q = 0; q < np; ++q) out += static_cast<double>(R[q]) * static_cast<double>(Cc[q]);
     for (int b = 0; b < 3; ++b) {
@@ -965,7 +1111,7 @@ Plan plan_gemm(int np, const int64_t* R, const int64_t* Cc, int64_t Kr, bool all
     return best;
 }
 Plan plan_gemm(int64_t R, int64_t Cc, int64_t Kr, bool allow_split, bool wide) {
-    return plan_gemm(1, &R, &Cc, Kr, allow_split, wide);
+    return plan_gemm(1, &R, &Cc, Kr, allow_split, wide, 0.70);
 }
 
 // 256-column tiles run on the four-wave kernel with kStages4 stages.
@@ -973,8 +1119,10 @@ constexpr int kStages4 = 5;
 
 template <bool TR, int BN>
 void launch_tile(const GemmLaunch& gl, int splits, hipStream_t s) {
-    if constexpr (BN == 256) {
-        hipLaunchKernelGGL((k_gemm4<TR, kStages4>), dim3(static_cast<unsigned>(gl.tiles * splits)), dim3(256), 0, s,
+    if constexpr (BN == 256 && !TR) {
+        hipLaunchKernelGGL(k_gemm_nt, dim3(static_cast<unsigned>(gl.tiles * splits)), dim3(256), 0, s, gl);
+    } else if constexpr (BN == 256) {
+        hipLaunchKernelGGL(k_gemm4<kStages4>, dim3(static_cast<unsigned>(gl.tiles * splits)), dim3(256), 0, s,
                            gl);
     } else {
         hipLaunchKernelGGL((k_gemm<TR, BN>), dim3(static_cast<unsigned>(gl.tiles * splits)), dim3(512), 0, s, gl);
@@ -1042,7 +1190,7 @@ size_t dw_workspace(int np, const DwProduct* d, int64_t M) {
         R[q] = d[q].K;
         Cc[q] = d[q].N;
     }
-    return split_workspace(plan_gemm(np, R, Cc, M, true, true), np, R, Cc);
+    return split_workspace(plan_gemm(np, R, Cc, M, true, true, 0.84), np, R, Cc);
 }
 
 hipError_t launch_dw(int np, const DwProduct* d, int64_t M, void* ws, hipStream_t s, const char* timer = nullptr) {
@@ -1051,7 +1199,7 @@ hipError_t launch_dw(int np, const DwProduct* d, int64_t M, void* ws, hipStream_
         R[q] = d[q].K;
         Cc[q] = d[q].N;
     }
-    const Plan pl = plan_gemm(np, R, Cc, M, true, true);
+    const Plan pl = plan_gemm(np, R, Cc, M, true, true, 0.84);
     const bool direct = pl.splits == 1;
     GemmArgs g[2];
     ReduceArgs fin[2];

@@ -1726,7 +1726,6 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
             bc.get(brow + S - 1, r, Bn, Cn);
 #pragma unroll
             for (int j = S - 1; j >= 0; --j) {
-                const int tl = q * S + j;
                 float Bv[4], Cv[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {

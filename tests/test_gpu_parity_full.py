@@ -402,3 +402,21 @@ def test_layer_workload_weight_grads_exact_sampled():
     ref = oracle.proj_dw(ub, dx16, r2.ravel(), c2.ravel()).reshape(len(rows), len(cols)) + gz @ wx.T
     check("dW_in[:,:D][sampled]", to_np(o["dW_in"])[np.ix_(rows, cols)], ref, 1e-4, rep)
     say("   rel-L2:", " ".join(f"{k}={v:.2e}" for k, v in rep.items()))
+
+
+@pytest.mark.parametrize("red", [8, 64, 72, 128, 136, 192, 256, 328])
+def test_proj_grad_dx_short_reductions(red):
+    """The dX form's 256 x 256 tiles over one to six 64-step stages (whole, and with a
+    tail of 8 steps), the last row and column blocks ragged; written and accumulated."""
+    M, K = 4095, 4088
+    say(f"[proj short dX] M={M} K={K} N={red}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4250 + red)
+    dZ = torch.randn(M, red, generator=g, device="cuda").to(torch.bfloat16)
+    W = (torch.randn(K, red, generator=g, device="cuda") / 32).to(torch.bfloat16)
+    _, dX = ssm.ssm_proj_grad(None, dZ, W, want_dW=False, want_dX=True)
+    _, dX2 = ssm.ssm_proj_grad(None, dZ, W, want_dW=False, want_dX=True, dX=dX.clone(), accum_dX=True)
+    torch.cuda.synchronize()
+    ref = dZ.float().cpu().double().numpy() @ W.float().cpu().double().numpy().T
+    check("dX", to_np(dX), ref, 1e-5)
+    check("dX accum", to_np(dX2), 2 * ref, 1e-5)
