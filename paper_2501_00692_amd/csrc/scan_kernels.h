@@ -152,32 +152,6 @@ __device__ __forceinline__ void lds_barrier() {
 // from moving them).
 __device__ __forceinline__ void wave_lds_sync() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
-// Load 4 consecutive states (r*4 .. r*4+3) of row `row` of a [rows][N] tensor.
-template <typename TI, bool N16>
-__device__ __forceinline__ void ld4(const TI* p, int64_t row, int r, int64_t N, bool valid,
-                                    float v[4]) {
-    if constexpr (N16) {
-        const int64_t o = valid ? row * 16 + r * 4 : 0;  // no branch around the load
-        if constexpr (sizeof(TI) == 2) {
-            const uint2 u = *reinterpret_cast<const uint2*>(p + o);
-            v[0] = valid ? __uint_as_float(u.x << 16) : 0.f;
-            v[1] = valid ? __uint_as_float(u.x & 0xffff0000u) : 0.f;
-            v[2] = valid ? __uint_as_float(u.y << 16) : 0.f;
-            v[3] = valid ? __uint_as_float(u.y & 0xffff0000u) : 0.f;
-        } else {
-            const float4 f = *reinterpret_cast<const float4*>(p + o);
-            v[0] = valid ? f.x : 0.f; v[1] = valid ? f.y : 0.f;
-            v[2] = valid ? f.z : 0.f; v[3] = valid ? f.w : 0.f;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int n = r * 4 + k;
-            v[k] = ldm(p, row * N + n, valid && n < N);
-        }
-    }
-}
-
 // Per-lane decay constants: cn = -e^{A_log} log2(e) (a = 2^{cn Delta}) and
 // wn = -e^{A_log} (da/dDelta = a wn), with A_log per (channel, state) or, for the
 // scalar-decay variant, per channel.  Padding states get cn = wn = 0.
@@ -1512,8 +1486,9 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                 for (int64_t p0 = sw_hi; p0 > sw_lo; p0 -= PB) {
                     typename RawIn<TI, PB>::Bits prb[PB], gyb[PB], zb[PB];
                     uint32_t mk[PB];
-                    // raw C bits: 4 bf16 (two words) or 4 fp32 words per step
-                    uint32_t cw[PB][sizeof(TI) == 2 ? 2 : 4];
+                    // raw C bits: 4 bf16 (two words) or 4 fp32 words per step; fewer than 16
+                    // states: each on its own (one that does not exist reads the row's first)
+                    uint32_t cw[PB][N16 && sizeof(TI) == 2 ? 2 : 4];
                     float Cb[PB][4];
 #pragma unroll
                     for (int u = 0; u < PB; ++u) {
@@ -1538,7 +1513,9 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                                 cw[u][3] = w.w;
                             }
                         } else {
-                            ld4<TI, N16>(Cp, bb * p.T + ps, r, p.N, ok, Cb[u]);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                cw[u][k] = ldbits(Cp, row * p.N + (r * 4 + k < p.N ? r * 4 + k : 0));
                         }
                     }
                     // keep the batch's loads ahead of its arithmetic
@@ -1555,6 +1532,12 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
                             } else {
 #pragma unroll
                                 for (int k = 0; k < 4; ++k) Cb[u][k] = __uint_as_float(cw[u][k] & m);
+                            }
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const uint32_t b = sizeof(TI) == 2 ? cw[u][k] << 16 : cw[u][k];
+                                Cb[u][k] = __uint_as_float(b & (r * 4 + k < p.N ? m : 0u));
                             }
                         }
                         const float pr = fin<TI>(prb[u], true);
@@ -1860,10 +1843,10 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
 
 // The tail reductions of the gradient in one launch: blocks [0, nbc) sum the
 // dB/dC split partials (as k_reduce_bc); the rest reduce the dA_log partials --
-// with one slice straight to the final [D][N] (or [D]) values, each thread
-// summing the (b, chunk) partials of one output in order (and, with one rate per
-// channel, over the states in order), else stage 1 of the sliced sum
-// (k_reduce_da1, with k_reduce_da2 launched after).
+// with one slice straight to the final [D][N] (or [D]) values, eight threads per
+// output summing contiguous eighths of its (b, chunk) partials (with one rate per
+// channel, of its (b, chunk, state) partials), added in order, else stage 1 of the
+// sliced sum (k_reduce_da1, with k_reduce_da2 launched after).
 [[maybe_unused]] __global__ __launch_bounds__(256) void k_reduce_tail(const ScanProblem p, int nbc) {
     const int tid = threadIdx.x;
     if (static_cast<int>(blockIdx.x) < nbc) {
@@ -1894,35 +1877,37 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
         }
         return;
     }
-    const int64_t i = static_cast<int64_t>(static_cast<int>(blockIdx.x) - nbc) * 256 + tid;
     const int64_t nq = p.nb * p.nc;
-    // acc += hbuf[(q N + n) D + d] for q = 0..nq-1 in order; the loads of a batch
-    // of 8 are issued before any of them is added
-    auto sum_q = [&](int64_t n, int64_t d, float acc) {
-        const int64_t stride = p.N * p.D;
-        const float* src = p.hbuf + n * p.D + d;
-        for (int64_t q0 = 0; q0 < nq; q0 += 8) {
+    if (p.nslice == 1) {
+        // 32 channels by 8 contiguous slices of the partials per workgroup (a thread per
+        // output left small problems one chain of up to 256 loads each, 8 in flight)
+        __shared__ float part[8][32];
+        const int64_t nd = (p.D + 31) / 32, blk = static_cast<int64_t>(blockIdx.x) - nbc;
+        const int64_t n = blk / nd, d = (blk % nd) * 32 + (tid & 31);  // one rate per channel: n = 0
+        const int sl = tid >> 5;
+        // the partials of (n, d): rows q of N D values; one rate per channel: every row (q, n)
+        const int64_t rows = p.ascalar ? nq * p.N : nq, stride = p.ascalar ? p.D : p.N * p.D;
+        const int64_t per = (rows + 7) / 8, q0 = min(rows, sl * per), q1 = min(rows, q0 + per);
+        const float* src = p.hbuf + n * p.D + (d < p.D ? d : 0);
+        float acc = 0.f;
+        for (int64_t qb = q0; qb < q1; qb += 8) {  // the loads of a batch are issued before its adds
             float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = q0 + j < nq ? src[(q0 + j) * stride] : 0.f;
+            for (int j = 0; j < 8; ++j) v[j] = qb + j < q1 ? src[(qb + j) * stride] : 0.f;
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc += v[j];
         }
-        return acc;
-    };
-    if (p.nslice == 1) {
-        if (p.ascalar) {
-            if (i >= p.D) return;
-            float acc = 0.f;
-            for (int64_t n = 0; n < p.N; ++n) acc = sum_q(n, i, acc);
-            p.dA_log[i] = acc;
-            return;
+        part[sl][tid & 31] = acc;
+        __syncthreads();
+        if (sl == 0 && d < p.D) {
+            float sum = part[0][tid];
+#pragma unroll
+            for (int j = 1; j < 8; ++j) sum += part[j][tid];
+            p.dA_log[p.ascalar ? d : d * p.N + n] = sum;
         }
-        if (i >= p.D * p.N) return;
-        const int64_t n = i / p.D, d = i % p.D;  // consecutive threads read consecutive channels
-        p.dA_log[d * p.N + n] = sum_q(n, d, 0.f);
         return;
     }
+    const int64_t i = static_cast<int64_t>(static_cast<int>(blockIdx.x) - nbc) * 256 + tid;
     if (i >= static_cast<int64_t>(p.nslice) * p.N * p.D) return;
     const int64_t d = i % p.D, n = (i / p.D) % p.N, sl = i / (p.D * p.N);
     const int64_t per = (nq + p.nslice - 1) / p.nslice;
@@ -2001,8 +1986,9 @@ hipError_t grad_impl(const ScanProblem& p, hipStream_t s) {
     }
     SSMK_TIMED("reduce", s);
     const int nbc = p.nsplit > 1 ? static_cast<int>(cdiv(p.nb * p.T * p.N, 256)) : 0;
-    const int64_t nda = p.nslice == 1 ? (p.ascalar ? p.D : p.D * p.N) : static_cast<int64_t>(p.nslice) * p.N * p.D;
-    hipLaunchKernelGGL(k_reduce_tail, dim3(static_cast<unsigned>(nbc) + cdiv(nda, 256)), dim3(256), 0, s, p, nbc);
+    const unsigned nda = p.nslice == 1 ? cdiv(p.D, 32) * static_cast<unsigned>(p.ascalar ? 1 : p.N)
+                                       : cdiv(static_cast<int64_t>(p.nslice) * p.N * p.D, 256);
+    hipLaunchKernelGGL(k_reduce_tail, dim3(static_cast<unsigned>(nbc) + nda), dim3(256), 0, s, p, nbc);
     if (p.nslice > 1) hipLaunchKernelGGL(k_reduce_da2, dim3(cdiv(p.D * p.N, 256)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
