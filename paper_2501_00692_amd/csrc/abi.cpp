@@ -153,7 +153,7 @@ LayerWs layer_ws(const ssm_desc* d, int64_t L, bool trunc, int64_t d_model) {
     const ssmk::DwProduct dwin{d_model, re ? nz : 2 * D, nullptr, 0, nullptr, 0, nullptr, false};
     size_t g = ssmk::gemm_dw2_workspace(M, dwx, dwin);
     for (size_t gi : {ssmk::gemm_dx_workspace(M, D, nx), ssmk::gemm_dx_workspace(M, d_model, 2 * D),
-                      re ? ssmk::gemm_dx_workspace(d_model, D, nx) : size_t(0)})
+                      re ? ssmk::gemm_hilo_workspace(d_model, D, nx) : size_t(0)})
         g = gi > g ? gi : g;
     off = up256(off + g);
     w.total = off;
@@ -668,13 +668,9 @@ ssm_status ssm_layer_grad(const ssm_desc* desc, int32_t mode, int64_t tbar, int6
         uint16_t* lo = hi + d_model * nx;
         e = ssmk::launch_layer_split(G, nz, d_model, D, nx, dW_in, 2 * D, hi, lo, s);
         if (e != hipSuccess) return hip_fail(e, "ssm_layer_grad split launch");
-        // dW_in[:, :D] = G[:, :D] + lo W_x^T, then += hi W_x^T
+        // dW_in[:, :D] = G[:, :D] + (hi + lo) W_x^T
         const uint16_t* Wx = static_cast<const uint16_t*>(W_x);
-        e = ssmk::launch_gemm_dx(d_model, D, nx, lo, nx, Wx, nx, dW_in, false, G, nullptr, 0, gws, s, 2 * D, nz,
-                                 "gemm_dwin_fix");
-        if (e != hipSuccess) return hip_fail(e, "ssm_layer_grad dW_in launch");
-        e = ssmk::launch_gemm_dx(d_model, D, nx, hi, nx, Wx, nx, dW_in, true, nullptr, nullptr, 0, gws, s, 2 * D,
-                                 0, "gemm_dwin_fix");
+        e = ssmk::launch_gemm_hilo(d_model, D, nx, hi, Wx, nx, dW_in, 2 * D, G, nz, gws, s);
         if (e != hipSuccess) return hip_fail(e, "ssm_layer_grad dW_in launch");
         if (need_dxt) {
             // dx_total = dx + dZx W_x^T; its bf16 copy replaces dx in Z, so that

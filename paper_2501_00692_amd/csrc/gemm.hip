@@ -1276,4 +1276,30 @@ hipError_t launch_gemm_dx(int64_t M, int64_t K, int64_t N, const uint16_t* dZ, i
     return hipGetLastError();
 }
 
+// The two parts as one product of 2 M rows whose partials (hi rows, then lo rows, per
+// split) are 2 x splits partials of M rows for the second stage, which adds them and
+// the addend: one GEMM launch and one reduction where a product per part took two of
+// each, every one of them too small to fill the GPU (768 x 1536 x 1568: 54 -> 35 us;
+// 2048 x 4096 x 4128, not split before: 213 -> 164).
+size_t gemm_hilo_workspace(int64_t M, int64_t K, int64_t N) {
+    const Plan pl = plan_gemm(2 * M, K, N, true, true);
+    return static_cast<size_t>(pl.splits) * 2 * M * K * sizeof(float);
+}
+
+hipError_t launch_gemm_hilo(int64_t M, int64_t K, int64_t N, const uint16_t* hilo, const uint16_t* W, int64_t ldw, float* dst,
+                            int64_t ldd, const float* add, int64_t ldadd, void* ws, hipStream_t s) {
+    const Plan pl = plan_gemm(2 * M, K, N, true, true);
+    GemmArgs g{2 * M, K, N, hilo, N, W, ldw, static_cast<float*>(ws), split_range(N, pl.splits), 0, 0, nullptr, nullptr, 0,
+               K, 0};
+    {
+        SSMK_TIMED("gemm_dwin_fix", s);
+        if (!launch_plan<false>(&g, 1, pl, s)) return hipErrorInvalidConfiguration;
+    }
+    SSMK_TIMED("splitk_reduce", s);
+    g.R = M;
+    const ReduceArgs fin{0, 0, nullptr, dst, 0, add, nullptr, 0, ldd, ldadd};
+    launch_reduce(&g, &fin, 1, 2 * pl.splits, s);
+    return hipGetLastError();
+}
+
 }  // namespace ssmk

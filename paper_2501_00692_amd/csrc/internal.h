@@ -196,4 +196,11 @@ hipError_t launch_gemm_dx(int64_t M, int64_t K, int64_t N, const uint16_t* dZ, i
                           uint16_t* out16, int64_t ld16, void* ws, hipStream_t s, int64_t ldx = 0,
                           int64_t ldadd = 0, const char* timer = nullptr);
 
+// dst[M][K] = add + (hi + lo) W^T for an fp32 [M][N] matrix held as two bf16 parts, hi
+// [M][N] followed by lo [M][N] (hilo), W [K][N] (ldw): the layer's reassociated
+// input-projection gradient.  ws holds gemm_hilo_workspace(M, K, N) bytes.
+size_t gemm_hilo_workspace(int64_t M, int64_t K, int64_t N);
+hipError_t launch_gemm_hilo(int64_t M, int64_t K, int64_t N, const uint16_t* hilo, const uint16_t* W, int64_t ldw, float* dst,
+                            int64_t ldd, const float* add, int64_t ldadd, void* ws, hipStream_t s);
+
 }  // namespace ssmk
