@@ -930,19 +930,13 @@ namespace {
 
 constexpr size_t kHeadLogitBytes = size_t(4) << 30;  // fp32 logits of one row block
 
-// Workspace of the head: per row block Norm(y) (bf16) and its transpose, 1/rms,
+// Workspace of the head: per row block Norm(y) (bf16), 1/rms,
 // Omega^T (bf16 [P][V]), the block's fp32 logits and bf16 logit gradients, dU
 // (fp32), and the GEMM workspace shared by the block's three products.
 struct HeadWs {
     int64_t rows;
-    size_t off_u, off_ut, off_r, off_omt, off_logit, off_g, off_du, off_gws, total;
+    size_t off_u, off_r, off_omt, off_logit, off_g, off_du, off_gws, total;
 };
-
-// Row blocks whose logits are computed by the weight-gradient GEMM form from
-// Norm(y)^T: a multiple of 8 rows (the form's 16-byte operand pieces) and at most
-// this many (the transpose's grid height).
-constexpr int64_t kHeadMaxTransRows = int64_t(65535) * 32;
-bool head_logits_dw(int64_t mb) { return mb % 8 == 0 && mb <= kHeadMaxTransRows; }
 
 HeadWs head_ws(int64_t M, int64_t P, int64_t V, int64_t block_rows) {
     HeadWs w{};
@@ -952,7 +946,6 @@ HeadWs head_ws(int64_t M, int64_t P, int64_t V, int64_t block_rows) {
     w.rows = rows;
     size_t o = 0;
     w.off_u = o; o = up256(o + size_t(rows) * P * 2);
-    w.off_ut = o; o = up256(o + size_t(rows) * P * 2);
     w.off_r = o; o = up256(o + size_t(rows) * 4);
     w.off_omt = o; o = up256(o + size_t(P) * V * 2);
     w.off_logit = o; o = up256(o + size_t(rows) * V * 4);
@@ -963,7 +956,7 @@ HeadWs head_ws(int64_t M, int64_t P, int64_t V, int64_t block_rows) {
     for (int64_t mb : {rows, M % rows}) {
         if (mb == 0) continue;
         for (size_t gi : {ssmk::gemm_dx_workspace(mb, V, P), ssmk::gemm_dx_workspace(mb, P, V),
-                          ssmk::gemm_dw_workspace(mb, V, P), ssmk::gemm_dw_workspace(P, mb, V)})
+                          ssmk::gemm_dw_workspace(mb, V, P)})
             g = gi > g ? gi : g;
     }
     w.off_gws = o; o = up256(o + g);
@@ -1014,7 +1007,6 @@ ssm_status ssm_lm_head_grad(int64_t M, int64_t P, int64_t V, uint32_t flags, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     uint16_t* u = reinterpret_cast<uint16_t*>(ws + w.off_u);
-    uint16_t* ut = reinterpret_cast<uint16_t*>(ws + w.off_ut);
     float* rinv = reinterpret_cast<float*>(ws + w.off_r);
     uint16_t* omt = reinterpret_cast<uint16_t*>(ws + w.off_omt);
     float* logit = reinterpret_cast<float*>(ws + w.off_logit);
@@ -1037,20 +1029,11 @@ ssm_status ssm_lm_head_grad(int64_t M, int64_t P, int64_t V, uint32_t flags, int
             HEAD_HIP(ssmk::launch_rms_fwd(yb, u, rinv, mb, P, s), "ssm_lm_head_grad norm");
         else
             HEAD_HIP(ssmk::launch_to_bf16(yb, u, mb * P, s), "ssm_lm_head_grad input");
-        // logits [mb][V] = u Omega^T = (u^T)^T (Omega^T), the reduction over P.  The
-        // weight-gradient form stages 32 whole rows of u^T and Omega^T per step, each
-        // read as whole cache lines, where the dX form stages 64-byte pieces of 256
-        // rows of u and Omega: 3.9 against 4.5 ms at 32,768 x 32,000 x 2,048, for a
-        // transpose of u of about 0.1 ms.  Other block heights take the dX form.
-        if (head_logits_dw(mb)) {
-            HEAD_HIP(ssmk::launch_transpose16(u, ut, mb, P, s), "ssm_lm_head_grad transpose");
-            HEAD_HIP(ssmk::launch_gemm_dw(P, mb, V, ut, mb, omt, V, logit, false, gws, s, "head_logits"),
-                     "ssm_lm_head_grad logits");
-        } else {
-            HEAD_HIP(ssmk::launch_gemm_dx(mb, V, P, u, P, om, P, logit, false, nullptr, nullptr, 0, gws, s, 0, 0,
-                                          "head_logits"),
-                     "ssm_lm_head_grad logits");
-        }
+        // logits [mb][V] = u Omega^T, the reduction over P: the dX form (3.88 ms at 32,768 x
+        // 32,000 x 2,048; the weight-gradient form from a transposed u 4.04 and 0.12)
+        HEAD_HIP(ssmk::launch_gemm_dx(mb, V, P, u, P, om, P, logit, false, nullptr, nullptr, 0, gws, s, 0, 0,
+                                      "head_logits"),
+                 "ssm_lm_head_grad logits");
         HEAD_HIP(ssmk::launch_head_xent(logit, V, targets + m0, loss + m0, G, V, mb, V, s),
                  "ssm_lm_head_grad loss");
         // dU [mb][P] = G Omega = G (Omega^T)^T: the dX form with the reduction over V
