@@ -992,9 +992,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
     float* dst = g.C + (g.direct ? 0 : static_cast<int64_t>(split) * g.R * g.Cc);
     const int64_t ldc = g.direct ? g.ldc : g.Cc;
-    if (g.direct && g.out16) store_block<false, true>(acc, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0, c0, wr, wc, lane);
-    else if (g.direct && g.accum) store_block<true, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
-    else store_block<false, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
+    const bool full = r0 + BM <= g.R && c0 + 256 <= g.Cc;
+    if (g.direct && g.out16) {
+        if (full)
+            store_tile<false, false, false, true, true>(acc, nullptr, 0, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0 + wr,
+                                                        c0 + wc, lane);
+        else
+            store_block<false, true>(acc, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0, c0, wr, wc, lane);
+    } else if (g.direct && g.accum) {
+        store_block<true, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
+    } else if (full) {
+        store_tile<false, false, true, false, true>(acc, dst, ldc, nullptr, 0, nullptr, 0, g.R, g.Cc, r0 + wr, c0 + wc, lane);
+    } else {
+        store_block<false, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
+    }
 }
 
 // Second stage of a split GEMM: result = sum over splits (in split order) +
@@ -1073,7 +1084,8 @@ constexpr int64_t kMaxWgs = (int64_t(1) << 23) - 1;
 // (one or two products) with reduction Kr, from a simple time model: rounds of 256
 // workgroups x the time of one workgroup's share (per 32 steps at full load,
 // measured: 0.57 us for 128 columns, 0.80 for 192; 256 on the four-wave kernels:
-// `wide_us`, 0.84 for dW, 0.70 for dX), plus the
+// `wide_us`, 0.84 for dW, 0.70 for dX from 1,024 reduction steps on; with fewer, the
+// filling of its stages and the store weigh more: priced as dW), plus the
 // HBM time of writing and re-reading the split partials (4 TB/s).  256-column
 // tiles (`wide`) for dW, and for dX when its epilogue is plain (no addend, and
 // either the fp32 result or its bf16 copy: the four-wave kernel's registers hold
@@ -1111,7 +1123,7 @@ Plan plan_gemm(int np, const int64_t* R, const int64_t* Cc, int64_t Kr, bool all
     return best;
 }
 Plan plan_gemm(int64_t R, int64_t Cc, int64_t Kr, bool allow_split, bool wide) {
-    return plan_gemm(1, &R, &Cc, Kr, allow_split, wide, 0.70);
+    return plan_gemm(1, &R, &Cc, Kr, allow_split, wide, Kr >= 1024 ? 0.70 : 0.84);
 }
 
 // 256-column tiles run on the four-wave kernel with kStages4 stages.
