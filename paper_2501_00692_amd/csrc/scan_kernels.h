@@ -351,12 +351,13 @@ struct SRow {
             }
         }
     }
-    // the 16 values as fp32 in scalar registers, here and not at their uses
+    // the 16 values as fp32 (packed bf16: unpacked here by the scalar unit, and not at
+    // their uses)
     __device__ __forceinline__ void unpack(float (&v)[16]) const {
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             v[k] = at(k);
-            asm volatile("" : "+s"(v[k]));
+            if constexpr (PACKED) asm volatile("" : "+s"(v[k]));
         }
     }
     __device__ __forceinline__ float at(int k) const {
@@ -464,43 +465,66 @@ __global__ __launch_bounds__(64) void k_chunk_aggr(const ScanProblem p) {
     // channels record zero sums
     const int64_t nseg = WANT_M ? p.L / SEG : 0;
     const int64_t sgb = (bb * p.nc + c) * nseg * p.Dp;
-    __shared__ float4 rows[WANT_M ? 64 : 1][5];  // the lanes' records (80-byte rows: no bank conflicts)
+    __shared__ float4 rows[WANT_M && N16 ? 64 : 1][5];  // the lanes' records (80-byte rows: no bank conflicts)
     auto put_seg = [&](int64_t q) {
-        // Through LDS, so that each store of the wave is 1 KB of consecutive records.
-        // Stored from the lanes' own registers, 16 bytes at every 64, the store path bound
-        // the kernel (slice workload, 8.6 GB of records: 5.3 -> 4.7 ms per call, 4.1 TB/s
-        // of its 19.2 GB where a plain copy reaches 4.7; T = 262,144, D = 3,072 without
-        // gate and softplus: 3.68 -> 2.79 ms).
-        wave_lds_sync();
+        if constexpr (N16) {
+            // Through LDS, so that each store of the wave is 1 KB of consecutive records.
+            // Stored from the lanes' own registers, 16 bytes at every 64, the store path
+            // bound the kernel (slice workload, 8.6 GB of records: 5.3 -> 4.7 ms per call,
+            // 4.1 TB/s of its 19.2 GB where a plain copy reaches 4.7; T = 262,144, D = 3,072
+            // without gate and softplus: 3.68 -> 2.79 ms).
+            wave_lds_sync();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rows[lane][i] = make_float4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
-        wave_lds_sync();
-        float4* rec = reinterpret_cast<float4*>(p.hseg + (sgb + q * p.Dp + d - lane) * 16) + lane;
+            for (int i = 0; i < 4; ++i) rows[lane][i] = make_float4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
+            wave_lds_sync();
+            float4* rec = reinterpret_cast<float4*>(p.hseg + (sgb + q * p.Dp + d - lane) * 16) + lane;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rec[64 * i] = rows[16 * i + (lane >> 2)][lane & 3];
+            for (int i = 0; i < 4; ++i) rec[64 * i] = rows[16 * i + (lane >> 2)][lane & 3];
+        } else {
+            // fewer than 16 states wait for their many scalar loads of B and C, and with LDS
+            // operations between those on every one of them (388 -> 487 us at b = 2, T =
+            // 20,266, D = 744, N = 8)
+            float4* rec = reinterpret_cast<float4*>(p.hseg + (sgb + q * p.Dp + d) * 16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) rec[i] = make_float4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
+        }
         (p.cseg + sgb + q * p.Dp)[static_cast<uint32_t>(d)] = dv ? static_cast<float>(sd) : 0.f;
     };
     // one step from its raw inputs and its rows of B and C
     auto step = [&](float xr, float pr, float dyr, float zr, const SRow<TI, N16>& cB,
                     const SRow<TI, N16>& cC) __attribute__((always_inline)) {
-        trans_begin();
+        // (fewer than 16 states: the rows are many small scalar loads, waited for at their
+        // uses; a group would wait for them all)
+        if constexpr (N16) trans_begin();
         const float dl = SP ? softplus_f(pr) : pr;
         if (p.bdelta) xr *= dl;  // input term Delta B x
         float g = 0.f;
         if constexpr (WANT_M) g = GATE ? dyr * zr * sigmoid_f(zr) : dyr;
         sd += static_cast<double>(dl);
-        float av[16], fB[16], fC[16];
+        if constexpr (N16) {
+            float av[16], fB[16], fC[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) av[i] = fexp2(cn[i] * dl);
-        cB.unpack(fB);
-        if constexpr (WANT_M) cC.unpack(fC);  // scalar work behind the exponentials
-        trans_end();
+            for (int i = 0; i < 16; ++i) av[i] = fexp2(cn[i] * dl);
+            cB.unpack(fB);
+            if constexpr (WANT_M) cC.unpack(fC);  // scalar work behind the exponentials
+            trans_end();
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            h[k] = fmaf(av[k], h[k], fB[k] * xr);
-            if constexpr (WANT_M) {
-                P[k] *= av[k];
-                m[k] = fmaf(g * fC[k], P[k], m[k]);
+            for (int k = 0; k < 16; ++k) {
+                h[k] = fmaf(av[k], h[k], fB[k] * xr);
+                if constexpr (WANT_M) {
+                    P[k] *= av[k];
+                    m[k] = fmaf(g * fC[k], P[k], m[k]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const float av = fexp2(cn[k] * dl);
+                h[k] = fmaf(av, h[k], cB.at(k) * xr);
+                if constexpr (WANT_M) {
+                    P[k] *= av;
+                    m[k] = fmaf(g * cC.at(k), P[k], m[k]);
+                }
             }
         }
     };
@@ -894,25 +918,34 @@ __global__ __launch_bounds__(64) void k_forward(const ScanProblem p) {
         static_cast<TI*>(p.y) + (rowb + t0) * p.D, 0, static_cast<int>(nl * p.D * sizeof(TI)), 0x00020000);
     auto step = [&](int tl, float xr, float pr, float zr, const SRow<TI, N16>& cB,
                     const SRow<TI, N16>& cC) __attribute__((always_inline)) {
-        trans_begin();
+        if constexpr (N16) trans_begin();
         const float dl = SP ? softplus_f(pr) : pr;
         if (p.bdelta) xr *= dl;  // input term Delta B x
         if constexpr (GATE) zr *= sigmoid_f(zr);
-        float yq[4], av[16], fB[16], fC[16];
+        float yq[4];
+        auto states = [&](auto av, auto b, auto cv) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) av[i] = fexp2(cn[i] * dl);
-        cB.unpack(fB);
-        cC.unpack(fC);
-        trans_end();
+            for (int i = 0; i < 4; ++i) {
+                float yp = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float yp = 0.f;
-#pragma unroll
-            for (int k = 4 * i; k < 4 * i + 4; ++k) {
-                h[k] = fmaf(av[k], h[k], fB[k] * xr);
-                yp = fmaf(fC[k], h[k], yp);
+                for (int k = 4 * i; k < 4 * i + 4; ++k) {
+                    h[k] = fmaf(av(k), h[k], b(k) * xr);
+                    yp = fmaf(cv(k), h[k], yp);
+                }
+                yq[i] = yp;
             }
-            yq[i] = yp;
+        };
+        if constexpr (N16) {
+            float av[16], fB[16], fC[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) av[k] = fexp2(cn[k] * dl);
+            cB.unpack(fB);
+            cC.unpack(fC);
+            trans_end();
+            states([&](int k) { return av[k]; }, [&](int k) { return fB[k]; }, [&](int k) { return fC[k]; });
+        } else {
+            states([&](int k) { return fexp2(cn[k] * dl); }, [&](int k) { return cB.at(k); },
+                   [&](int k) { return cC.at(k); });
         }
         float y = (yq[0] + yq[1]) + (yq[2] + yq[3]);
         if constexpr (GATE) y *= zr;
