@@ -149,15 +149,17 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // lane's own X: the product needs no data movement and its result is again in
 // the output layout.  m4 holds the lane's operand values of M (M[i][4q + kb], a
 // float4 of row i; M[4q + kb][i] for M^T X, see vals_t), loaded ahead by the
-// caller; `add` is added to the product.
+// caller; `add` is added to the product.  The four sums of four products are added as
+// a tree and `add` last: a chain of instructions from `add` on would be shorter by the
+// adds but round every step at add's magnitude (states and adjoints against 64 bits:
+// 12 and 8 % more error).
 __device__ __forceinline__ f4 mul_vals(const float4 m4, f4 X, f4 add = f4{0.f, 0.f, 0.f, 0.f}) {
-    // two chains of two instructions (each waits for the one before it)
-    f4 z = {0.f, 0.f, 0.f, 0.f};
-    add = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.x, X[0], add, 0, 0, 0);
-    z = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.z, X[2], z, 0, 0, 0);
-    add = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.y, X[1], add, 0, 0, 0);
-    z = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.w, X[3], z, 0, 0, 0);
-    return add + z;
+    const f4 z = {0.f, 0.f, 0.f, 0.f};
+    const f4 p0 = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.x, X[0], z, 0, 0, 0);
+    const f4 p1 = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.y, X[1], z, 0, 0, 0);
+    const f4 p2 = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.z, X[2], z, 0, 0, 0);
+    const f4 p3 = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.w, X[3], z, 0, 0, 0);
+    return ((p0 + p1) + (p2 + p3)) + add;
 }
 // Lane 16 q + i's operand values of M^T X.
 __device__ __forceinline__ float4 vals_t(const float* M, int i, int q) {

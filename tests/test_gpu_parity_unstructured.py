@@ -73,6 +73,32 @@ def test_unstructured_step_batches(T, P, chunk, tbar):
     say("   rel-L2:", " ".join(f"{k}={v:.2e}" for k, v in rep.items()))
 
 
+def test_unstructured_sums_before_the_added_term():
+    """The products of a step and of a chunk carry are summed before the term they are
+    added to.  16 ones next to 2^26 (a multiple of 8 in fp32): summed first they give
+    2^26 + 16 exactly; added to it in parts of 4 or fewer they vanish.  All of it, the
+    states in dC (dy picks row 0) and the adjoints in dB, is exact in fp32, so the
+    result is the oracle's to the bit: chunk 0 has the step (t = 0) and the forward
+    carry, chunk 1 (t = 16) the backward one."""
+    T, P, big = 48, 16, float(1 << 26)
+    say("[unstructured exact sums]")
+    A = torch.eye(16).repeat(1, T, 1, 1)
+    A[0, 0] = A[0, 16] = 1.0
+    B, C = torch.zeros(1, T, 16, P), torch.zeros(1, T, P, 16)
+    x, dy = torch.zeros(1, T, P), torch.zeros(1, T, P)
+    x[..., 0] = dy[..., 0] = 1.0
+    B[0, 0, :, 0] = big          # B_0 x_0 = 2^26
+    C[0, 16, 0] = big / 16       # v_16, so that A_16^T v_16 = 2^26
+    C[0, 32, 0] = 1.0            # v_32 = 1
+    inp = {k: v.cuda() for k, v in dict(A=A, B=B, C=C, x=x, dy=dy, h0=torch.ones(1, 16)).items()}
+    o = _gpu(inp, 0, 16, want_dh0=True)
+    h = _host(inp)
+    ref = un_bptt(h["A"], h["B"], h["C"], h["x"], h["dy"], h["h0"])
+    assert ref["dC"][0, 0, 0, 0] == big + 16 and ref["dB"][0, 15, 0, 0] == big + 16
+    for k in ("dB", "dC", "dh0"):
+        assert np.array_equal(to_np(o[k]), ref[k]), k
+
+
 def test_unstructured_workload_full_every_entry():
     """b = 8, T = 16,384, P = 64, N = 16 (chunks of 64): every output."""
     b, T, P, _ = UN_WORKLOADS["unstructured"]
