@@ -97,7 +97,9 @@ typedef struct {
 } ssm_desc;
 
 /* Workspace bytes needed by ssm_adjoint_forward / ssm_adjoint_grad for `desc`
- * (and `mode`, `tbar`).  Returns SSM_OK and writes *bytes, or an error status. */
+ * (and `mode`, `tbar`).  Returns SSM_OK and writes *bytes, or an error status.
+ * With chunk 0 the size also covers every smaller batch, seqlen and channels whose
+ * default chunk is shorter (here and in the other size queries that take `desc`). */
 ssm_status ssm_adjoint_forward_workspace_size(const ssm_desc* desc, size_t* bytes);
 ssm_status ssm_adjoint_grad_workspace_size(const ssm_desc* desc, int32_t mode, int64_t tbar,
                                            size_t* bytes);
@@ -147,9 +149,8 @@ ssm_status ssm_adjoint_grad(const ssm_desc* desc, int32_t mode, int64_t tbar, co
  * outputs); the scratch is a 64 MiB device array inside the library, one per
  * GPU, held from the first call on that GPU until the process ends.  The call
  * allocates nothing.  It returns SSM_ERR_WORKSPACE, before anything is
- * enqueued, when the problem needs more scratch than that (the workspace size
- * that ssm_adjoint_grad_workspace_size reports for the same arguments is what
- * it needs).  Every call on one GPU uses that GPU's single array: calls that
+ * enqueued, when the problem needs more scratch than that (exactly when
+ * ssm_adjoint_grad_workspace_size reports more for the same arguments).  Every call on one GPU uses that GPU's single array: calls that
  * can overlap on one GPU (different streams, or host threads) race and must be
  * serialised by the caller; calls on one stream are ordered.  No part of the
  * scratch needs to start at zero. */

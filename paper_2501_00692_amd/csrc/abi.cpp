@@ -110,6 +110,14 @@ ssmk::ScanProblem make_problem(const ssm_desc* d, int64_t L, int64_t nc) {
     return p;
 }
 
+// What a size query adds to a call's own scan workspace of `own` bytes, so that with
+// chunk 0 the answer covers the smaller shapes too (whose chunk may be shorter).
+size_t covers_smaller(const ssm_desc* d, int64_t L, ssmk::WsKind kind, bool trunc, size_t own) {
+    if (d->chunk != 0) return 0;
+    const size_t c = ssmk::shorter_chunks_workspace(d->batch, d->seqlen, d->channels, d->dstate, L, kind, trunc);
+    return c > own ? c - own : 0;
+}
+
 // Workspace of the whole-layer call: the scan workspace, then the bf16 operands
 // of the projection products, fp32 scan outputs that the caller did not supply,
 // the reassociated input-projection gradient's G and its bf16 hi/lo parts
@@ -171,9 +179,10 @@ ssm_status ssm_adjoint_forward_workspace_size(const ssm_desc* desc, size_t* byte
     ssm_status st = check_desc(desc, &L, &nc);
     if (st) return st;
     if (!bytes) return fail(SSM_ERR_NULL, "bytes is NULL");
-    *bytes = ssmk::scan_workspace(desc->batch, desc->seqlen, desc->channels, desc->dstate, L,
-                                  false, false)
-                 .total;
+    const size_t own = ssmk::scan_workspace(desc->batch, desc->seqlen, desc->channels, desc->dstate, L,
+                                            false, false)
+                           .total;
+    *bytes = own + covers_smaller(desc, L, ssmk::WsKind::forward, false, own);
     return SSM_OK;
 }
 
@@ -186,9 +195,10 @@ ssm_status ssm_adjoint_grad_workspace_size(const ssm_desc* desc, int32_t mode, i
     st = check_mode(desc, mode, tbar, &trunc);
     if (st) return st;
     if (!bytes) return fail(SSM_ERR_NULL, "bytes is NULL");
-    *bytes = ssmk::scan_workspace(desc->batch, desc->seqlen, desc->channels, desc->dstate, L,
-                                  true, trunc)
-                 .total;
+    const size_t own = ssmk::scan_workspace(desc->batch, desc->seqlen, desc->channels, desc->dstate, L,
+                                            true, trunc)
+                           .total;
+    *bytes = own + covers_smaller(desc, L, ssmk::WsKind::grad, trunc, own);
     return SSM_OK;
 }
 
@@ -375,7 +385,10 @@ ssm_status ssm_adjoint_grad_pairs_workspace_size(const ssm_desc* desc, int32_t m
     st = check_mode(desc, mode, tbar, &trunc);
     if (st) return st;
     if (!bytes) return fail(SSM_ERR_NULL, "bytes is NULL");
-    *bytes = ssmk::pairs_workspace(desc->batch, desc->seqlen, desc->channels, desc->dstate, L).total;
+    const ssmk::PairsWorkspace w = ssmk::pairs_workspace(desc->batch, desc->seqlen, desc->channels,
+                                                         desc->dstate, L);
+    // the carries and Delta sums (up to off_dl) and the dA_log partials depend on the chunk
+    *bytes = w.total + covers_smaller(desc, L, ssmk::WsKind::pairs, trunc, w.off_dl + (w.total - w.off_dAtmp));
     return SSM_OK;
 }
 
@@ -572,7 +585,8 @@ ssm_status ssm_layer_grad_workspace_size(const ssm_desc* desc, int32_t mode, int
     if (st) return st;
     if (!bytes) return fail(SSM_ERR_NULL, "bytes is NULL");
     if (d_model < 1) return fail(SSM_ERR_SHAPE, "d_model must be >= 1");
-    *bytes = layer_ws(desc, L, trunc, d_model).total;
+    const LayerWs w = layer_ws(desc, L, trunc, d_model);
+    *bytes = w.total + covers_smaller(desc, L, ssmk::WsKind::grad, trunc, w.scan_total);
     return SSM_OK;
 }
 
@@ -802,7 +816,9 @@ ssm_status ssm_stack_grad_workspace_size(const ssm_desc* desc, int64_t K, int32_
     ssm_status st = check_stack(desc, K, grad, mode, tbar, &L, &trunc);
     if (st) return st;
     if (!bytes) return fail(SSM_ERR_NULL, "bytes is NULL");
-    *bytes = stack_ws(desc, K, L, trunc).total;
+    const StackWs w = stack_ws(desc, K, L, trunc);
+    *bytes = w.total + covers_smaller(desc, L, ssmk::WsKind::forward, false, w.fws_bytes) +
+             covers_smaller(desc, L, ssmk::WsKind::grad, trunc, layer_ws(desc, L, trunc, desc->channels).scan_total);
     return SSM_OK;
 }
 

@@ -108,6 +108,12 @@ void choose_split(int64_t nb, int64_t D, int64_t nc, int* nsplit, int* tiles_per
 int choose_nslice(int64_t nb, int64_t nc);
 ScanWorkspace scan_workspace(int64_t nb, int64_t T, int64_t D, int64_t N, int64_t L, bool grad,
                              bool trunc);
+// Scan workspace bytes that cover every chunk-0 call of a batch, seqlen and channels no
+// larger than these whose default chunk is shorter than L, this shape's own (0: none
+// is); `pairs`: of the regions of the pair formulation that depend on the chunk (its
+// carries, Delta sums and dA_log partials).
+enum class WsKind { forward, grad, pairs };
+size_t shorter_chunks_workspace(int64_t nb, int64_t T, int64_t D, int64_t N, int64_t L, WsKind kind, bool trunc);
 void bind_workspace(ScanProblem& p, void* ws, const ScanWorkspace& w);
 
 hipError_t launch_forward(const ScanProblem& p, hipStream_t s);

@@ -2,6 +2,8 @@
 // the gradient dispatch to the per-(dtype, mode) translation units.
 #include "scan_kernels.h"
 
+#include <algorithm>
+
 namespace ssmk {
 namespace {
 
@@ -105,6 +107,36 @@ ScanWorkspace scan_workspace(int64_t nb, int64_t T, int64_t D, int64_t N, int64_
     if (grad) off = align_up(off + 1024);
     w.total = off;
     return w;
+}
+
+// A call with the default chunk of 32 or 64 can need more than a larger one with a
+// longer chunk (twice the carries: forward, D = 512, 2.36 MB at T = 4,096 against 1.22
+// at 4,128), and a workspace made for a program's largest call has to serve its
+// smaller ones.  Every term of scan_workspace is bounded over the smaller shapes that
+// default_chunk gives the chunk l: at most min(b nc, 512) chunks and min(b nc ceil(D/64),
+// 512) chunks times 64-channel blocks, nc = min(T/l, 2l); one split per block there.
+// Below 32 MiB in all.
+size_t shorter_chunks_workspace(int64_t nb, int64_t T, int64_t D, int64_t N, int64_t L, WsKind kind, bool trunc) {
+    size_t most = 0;
+    const int64_t groups = (D + 63) / 64;
+    for (int64_t l = 32; l < L && l < kDefaultChunk; l *= 2) {
+        const int64_t nc = std::min((T + l - 1) / l, 2 * l);
+        const int64_t q = std::min<int64_t>(nb * nc, 512), blocks = std::min<int64_t>(nb * nc * groups, 512);
+        const int64_t rows = std::min(nb * nc * D, blocks * 64);  // b nc D
+        const bool grad = kind == WsKind::grad;
+        auto bytes = [](int64_t n, int64_t each) { return align_up(static_cast<size_t>(n * each)); };
+        size_t s = bytes(rows * N, 4) + bytes(rows, 8);  // hbuf, sdel
+        if (kind != WsKind::forward)  // dAtmp: over 256 chunks (one block of channels) in slices, else one
+            s += bytes(std::max(std::min(D, blocks * 64), q > 256 ? choose_nslice(1, q) * std::min<int64_t>(D, 64) : 0) * N, 4);
+        if (grad) {
+            s += bytes(rows * N, 4) + 1024;  // mbuf, sink
+            s += bytes(blocks * 64 * (l / grad_segment(l)), 64) + bytes(blocks * 64 * (l / grad_segment(l)), 4);  // hseg, cseg
+            if (trunc) s += bytes(rows + std::min<int64_t>(nb * D, 512 * 64), 8);  // psum
+            if (groups > 1) s += 2 * bytes(blocks * l * N, 4);                     // pB, pC
+        }
+        most = std::max(most, s);
+    }
+    return most;
 }
 
 void bind_workspace(ScanProblem& p, void* ws, const ScanWorkspace& w) {

@@ -125,6 +125,83 @@ def test_workspace_queries(lib):
     assert n.value > 0
 
 
+def needed(lib, entry, d, tbar=0):
+    """Workspace bytes the call itself asks for (from its refusal of an empty workspace)."""
+    if entry == "forward":
+        rc = lib.ssm_adjoint_forward(ctypes.byref(d), FAKE, FAKE, FAKE, FAKE, FAKE, None, None, FAKE, None, FAKE, 0, None)
+    else:
+        rc = grad_call(lib, d, mode=1 if tbar else 0, tbar=tbar, ws_bytes=0,
+                       entry="ssm_adjoint_grad" + ("_pairs" if entry == "pairs" else ""))
+    assert rc == 5
+    return int(re.search(r"(\d+) needed", ssm.last_error()).group(1))
+
+
+def queried(lib, entry, d, tbar=0):
+    n = ctypes.c_size_t()
+    mode = (1 if tbar else 0, tbar)
+    rc = {"forward": lambda: lib.ssm_adjoint_forward_workspace_size(ctypes.byref(d), ctypes.byref(n)),
+          "grad": lambda: lib.ssm_adjoint_grad_workspace_size(ctypes.byref(d), *mode, ctypes.byref(n)),
+          "pairs": lambda: lib.ssm_adjoint_grad_pairs_workspace_size(ctypes.byref(d), *mode, ctypes.byref(n)),
+          "layer": lambda: lib.ssm_layer_grad_workspace_size(ctypes.byref(d), *mode, 64, ctypes.byref(n)),
+          "stack": lambda: lib.ssm_stack_grad_workspace_size(ctypes.byref(d), 2, 1, *mode, ctypes.byref(n))}[entry]()
+    assert rc == 0, ssm.last_error()
+    return n.value
+
+
+@pytest.mark.parametrize("b,T,D,chunk", [
+    (1, 1, 1, 32), (1, 2048, 64, 32), (1, 2049, 64, 64), (1, 8192, 64, 64), (1, 8193, 64, 128),  # carry chains of 64 and 128
+    (1, 1024, 1024, 32), (1, 1024, 1025, 64), (1, 1024, 2048, 64), (1, 1024, 2049, 128),         # 512 workgroups
+    (512, 32, 64, 32), (513, 32, 64, 128), (512, 64, 64, 64), (512, 65, 64, 128)])
+def test_default_chunk_rule(lib, b, T, D, chunk):
+    """Chunk 0 is 32, 64 or 128 on either side of each threshold (told apart by the carries' size)."""
+    size = lambda c: needed(lib, "forward", desc(batch=b, seqlen=T, channels=D, chunk=c))
+    assert size(0) == size(chunk)
+    assert T <= 32 or len({size(c) for c in (32, 64, 128)}) > 1
+
+
+@pytest.mark.parametrize("entry,tbar", [("forward", 0), ("grad", 0), ("grad", 9), ("pairs", 0)])
+def test_default_chunk_workspace_covers_smaller_calls(lib, entry, tbar):
+    """With chunk 0, the size of a call is enough for every smaller batch, seqlen and
+    channels (to which the library may give a shorter chunk)."""
+    import random
+    rng = random.Random(4)
+    shapes = [((8, 179, 634), (8, 179, 641)), ((1, 8124, 127), (1, 8207, 127)), ((39, 415, 44), (40, 415, 44)),
+              ((1, 4096, 512), (1, 4128, 512)), ((1, 2048, 64), (1, 2049, 64)), ((512, 32, 64), (513, 32, 64)),
+              ((1, 1024, 1024), (3, 1 << 20, 1024)), ((8, 1019, 118), (8, 1030, 118)), ((8, 2045, 10), (8, 2066, 10))]
+    for _ in range(3000):
+        big = [int(2 ** rng.uniform(0, e)) for e in (10, 15, 12)]
+        f = rng.choice([0.99, 0.9, rng.random()])
+        shapes.append(([max(1, int(s * (f if rng.random() < 0.5 else 1))) for s in big], big))
+    short = 0
+    for small, big in shapes:
+        for N in (16, 5):
+            ds, db = (desc(batch=s[0], seqlen=s[1], channels=s[2], dstate=N) for s in (small, big))
+            if tbar >= small[1]:
+                continue
+            need = needed(lib, entry, ds, tbar)
+            assert queried(lib, entry, ds, tbar) >= need
+            ds.chunk = 128
+            if need == needed(lib, entry, ds, tbar):
+                continue  # a chunk of 128: sizes as a fixed chunk gives them
+            short += 1
+            assert queried(lib, entry, db, tbar) >= need, (small, big, N)
+            if entry == "grad":  # the fixed array of the no-allocation entry: size and need agree on it
+                assert (queried(lib, entry, db, tbar) > 64 << 20) == (needed(lib, entry, db, tbar) > 64 << 20)
+    assert short > 500
+
+
+def test_default_chunk_workspace_of_layer_and_stack(lib):
+    """The layer's and the stack's sizes grow by the same bytes as the scan calls inside them."""
+    d = dict(in_dtype=ssm.SSM_BF16)
+    for b, T, D, L in [(1, 4128, 512, 128), (8, 1088, 128, 128), (1, 2112, 64, 64), (1, 256, 64, 32), (2, 4096, 1536, 128)]:
+        for tbar in (0, 9):
+            extra = {e: queried(lib, e, desc(batch=b, seqlen=T, channels=D, **d), tbar) -
+                     queried(lib, e, desc(batch=b, seqlen=T, channels=D, chunk=L, **d), tbar)
+                     for e in ("forward", "grad", "layer", "stack")}
+            assert extra["layer"] == extra["grad"] and extra["stack"] == extra["grad"] + extra["forward"]
+            assert (extra["forward"] > 0) == (L > 32 and D < 1536)
+
+
 def test_proj_errors(lib):
     call = lambda M, K, N, X=FAKE, dZ=FAKE, W=None, dW=FAKE, dX=None, ldx=None: lib.ssm_proj_grad(
         M, K, N, X, ldx if ldx is not None else K, dZ, N, W, N, dW, dX, 0, FAKE, 1 << 40, None)
