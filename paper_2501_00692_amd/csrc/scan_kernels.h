@@ -432,9 +432,13 @@ struct ChunkRows {
 // per step for all 16 states.  The raw inputs x, Delta, dy, z are loaded one
 // 4-step group ahead.  Steps past the end of the sequence (in the last group)
 // have Delta = x = g = 0 and leave h, P, m and the sum unchanged.
+// The gradient's forms with 16 states hold h, P, m and the rates in 64 registers; with a
+// step's 16 decays beside them they took 132 to 137 and three waves per SIMD.  Decays in
+// two groups of eight and the limit of four waves: 112 to 123, 2.24 -> 2.09 ms (T =
+// 131,072, D = 4,096, bf16, gate), 515 -> 448 us (b = 2, T = 32,768, D = 1,536, fp32).
 // ---------------------------------------------------------------------------
 template <typename TI, bool SP, bool GATE, bool WANT_M, bool N16, int SEG>
-__global__ __launch_bounds__(64) void k_chunk_aggr(const ScanProblem p) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WANT_M && N16 ? 4 : 1, 8))) void k_chunk_aggr(const ScanProblem p) {
     constexpr int G = 4;  // steps per group
     static_assert(SEG % G == 0, "segments are whole groups");
     const int lane = threadIdx.x;
@@ -502,18 +506,26 @@ __global__ __launch_bounds__(64) void k_chunk_aggr(const ScanProblem p) {
         if constexpr (WANT_M) g = GATE ? dyr * zr * sigmoid_f(zr) : dyr;
         sd += static_cast<double>(dl);
         if constexpr (N16) {
-            float av[16], fB[16], fC[16];
+            constexpr int GW = WANT_M ? 8 : 16;  // decays per group
+            float fB[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) av[i] = fexp2(cn[i] * dl);
-            cB.unpack(fB);
-            if constexpr (WANT_M) cC.unpack(fC);  // scalar work behind the exponentials
-            trans_end();
+            for (int g0 = 0; g0 < 16; g0 += GW) {
+                float av[GW];
+                if (g0 > 0) trans_begin();
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                h[k] = fmaf(av[k], h[k], fB[k] * xr);
-                if constexpr (WANT_M) {
-                    P[k] *= av[k];
-                    m[k] = fmaf(g * fC[k], P[k], m[k]);
+                for (int i = 0; i < GW; ++i) av[i] = fexp2(cn[g0 + i] * dl);
+                if constexpr (!WANT_M) cB.unpack(fB);  // scalar work behind the exponentials
+                trans_end();
+#pragma unroll
+                for (int i = 0; i < GW; ++i) {
+                    const int k = g0 + i;
+                    if constexpr (WANT_M) {
+                        h[k] = fmaf(av[i], h[k], cB.at(k) * xr);
+                        P[k] *= av[i];
+                        m[k] = fmaf(g * cC.at(k), P[k], m[k]);
+                    } else {
+                        h[k] = fmaf(av[i], h[k], fB[k] * xr);
+                    }
                 }
             }
         } else {
