@@ -784,9 +784,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // Epilogue of a wave's 128 x 128 block (4 x 4 MFMA tiles) at (row0, col0) of the 256 x
 // 256 tile at (r0, c0), through a buffer resource over the tile's rows that exist:
 // columns past the output take an offset past every range, so the block's last rows and
-// columns need no branches (with a branch per element on edge tiles, accumulators spilled:
-// 8191 x 1528 x 1560, one round of tiles, 61 us against 51).  ACC: C += result; O16: the
-// result as bf16 into o16 instead.
+// columns need no branches.  Rows outside, columns inside: the offsets of one tile's 16
+// rows are held at a time, not those of all 64 (which spilled accumulators).  ACC: C +=
+// result; O16: the result as bf16 into o16 instead.
 template <bool ACC, bool O16>
 __device__ __forceinline__ void store_block(const f32x16 (&acc)[4][4], float* dst, int64_t ldc, uint16_t* o16, int64_t ld16,
                                             int64_t R, int64_t Cc, int64_t r0, int64_t c0, int row0, int col0, int lane) {
@@ -797,11 +797,11 @@ __device__ __forceinline__ void store_block(const f32x16 (&acc)[4][4], float* ds
                                                    min<int64_t>(BM, R - r0) * ld * EL);
     const uint32_t rb = static_cast<uint32_t>(ld * EL);  // bytes per row; a tile's offsets fit 31 bits (ld <= 2^20)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int col = col0 + j * 32 + (lane & 31);
-        const bool in = c0 + col < Cc;
+    for (int i = 0; i < 4; ++i) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int j = 0; j < 4; ++j) {
+            const int col = col0 + j * 32 + (lane & 31);
+            const bool in = c0 + col < Cc;
             uint32_t o[16];
             float e[16];
 #pragma unroll
@@ -895,6 +895,14 @@ struct NtOps {
     }
 };
 
+// EP: the result written as fp32 (or as a split's partial), added to C, or written as
+// bf16; FULL: 256 divides the output's rows and columns.  Each form is a kernel of its
+// own: with all of them in one, and with a full and an edge form of the fp32 store
+// behind a branch, 16 or 17 accumulator registers went to scratch before the epilogue on
+// every tile (41,048 x 2,000 x 160 108 -> 102 us, 65,536 x 4,096 x 512 397 -> 380,
+// 65,536 x 4,088 x 512 477 -> 445, 262,144 x 4,096 x 4,128 7.87 -> 7.78 ms).
+enum class Ep { f32, accum, bf16 };
+template <Ep EP, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_nt(const GemmLaunch gl) {
     constexpr int MI = 4, NJ = 4;
     const int tid = threadIdx.x;
@@ -992,16 +1000,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
     float* dst = g.C + (g.direct ? 0 : static_cast<int64_t>(split) * g.R * g.Cc);
     const int64_t ldc = g.direct ? g.ldc : g.Cc;
-    const bool full = r0 + BM <= g.R && c0 + 256 <= g.Cc;
-    if (g.direct && g.out16) {
-        if (full)
+    if constexpr (EP == Ep::bf16) {
+        if (FULL || (r0 + BM <= g.R && c0 + 256 <= g.Cc))
             store_tile<false, false, false, true, true>(acc, nullptr, 0, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0 + wr,
                                                         c0 + wc, lane);
         else
             store_block<false, true>(acc, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0, c0, wr, wc, lane);
-    } else if (g.direct && g.accum) {
+    } else if constexpr (EP == Ep::accum) {
         store_block<true, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
-    } else if (full) {
+    } else if constexpr (FULL) {
         store_tile<false, false, true, false, true>(acc, dst, ldc, nullptr, 0, nullptr, 0, g.R, g.Cc, r0 + wr, c0 + wc, lane);
     } else {
         store_block<false, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
@@ -1132,7 +1139,14 @@ constexpr int kStages4 = 5;
 template <bool TR, int BN>
 void launch_tile(const GemmLaunch& gl, int splits, hipStream_t s) {
     if constexpr (BN == 256 && !TR) {
-        hipLaunchKernelGGL(k_gemm_nt, dim3(static_cast<unsigned>(gl.tiles * splits)), dim3(256), 0, s, gl);
+        const dim3 grid(static_cast<unsigned>(gl.tiles * splits));
+        const bool full = gl.p[0].R % BM == 0 && gl.p[0].Cc % 256 == 0;
+        if (gl.p[0].direct && gl.p[0].out16) {
+            if (full) hipLaunchKernelGGL((k_gemm_nt<Ep::bf16, true>), grid, dim3(256), 0, s, gl);
+            else hipLaunchKernelGGL((k_gemm_nt<Ep::bf16, false>), grid, dim3(256), 0, s, gl);
+        } else if (gl.p[0].direct && gl.p[0].accum) hipLaunchKernelGGL((k_gemm_nt<Ep::accum, false>), grid, dim3(256), 0, s, gl);
+        else if (full) hipLaunchKernelGGL((k_gemm_nt<Ep::f32, true>), grid, dim3(256), 0, s, gl);
+        else hipLaunchKernelGGL((k_gemm_nt<Ep::f32, false>), grid, dim3(256), 0, s, gl);
     } else if constexpr (BN == 256) {
         hipLaunchKernelGGL(k_gemm4<kStages4>, dim3(static_cast<unsigned>(gl.tiles * splits)), dim3(256), 0, s,
                            gl);

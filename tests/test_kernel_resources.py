@@ -80,3 +80,12 @@ def test_chunk_aggregates_hold_four_waves(kernels):
     assert len(got) == 8
     for name, k in got:
         assert k[".vgpr_count"] <= 128 and k[".private_segment_fixed_size"] == 0, name
+
+
+def test_gemm_keeps_its_accumulators(kernels):
+    """The 256 x 256 kernels hold 256 accumulators in the AGPRs and everything else in the
+    VGPRs: nothing in scratch, in any epilogue form."""
+    got = [*_pick(kernels, "9k_gemm_ntI"), *_pick(kernels, "7k_gemm4I")]
+    assert len(got) >= 4
+    for name, k in got:
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
