@@ -320,13 +320,15 @@ def test_proj_grad_wide_dx_tiles_sampled():
 
 @pytest.mark.parametrize("form", ["dW", "dX"])
 def test_proj_grad_every_main_loop_residue(form):
-    """The four-wave kernel's main loop runs four passes over its five-stage LDS
+    """The four-wave dW kernel's main loop runs four passes over its five-stage LDS
     ring per iteration (20 reduction steps of 32), then single passes, then the
-    last stages one by one.  Reductions of 32 n + 7 for n = 24..43 put every
-    residue of that schedule (and a ragged last stage) into one 256 x 256-tile
-    launch: dW of 2048 x 8192 (256 output tiles) and plain dX of 4096 x 4096 (256
-    output tiles, so both take 256-column tiles and no split; dX's reduction must
-    be a multiple of 8, so there it is 32 n + 8).  Sampled entries,
+    last stages one by one; the dX kernel's runs four stages of 64 steps per
+    iteration, alternating between its two slots, then up to three more.
+    Reductions of 32 n + 7 for n = 24..43 put every residue of both schedules (and
+    a ragged last stage) into one 256 x 256-tile launch: dW of 2048 x 8192 (256
+    output tiles) and plain dX of 4096 x 4096 (256 output tiles, so both take
+    256-column tiles and no split; dX's reduction must be a multiple of 8, so there
+    it is 32 n + 8).  Sampled entries,
     each output's corners included, against the oracle's plain loops."""
     g = torch.Generator(device="cuda")
     g.manual_seed(4245 if form == "dW" else 4246)

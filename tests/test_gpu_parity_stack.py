@@ -65,6 +65,30 @@ def test_stack_split_projections():
     say("   rel-L2 max:", f"{max(rep.values()):.2e}")
 
 
+@pytest.mark.parametrize("M,D", [(8191, 1528), (8192, 1536), (8192, 1528), (8191, 1536)])
+def test_stack_forward_wide_tiles(M, D):
+    """The forward's x, z and Delta_pre products at sizes that take 256 x 256 tiles
+    (6 x 32 of them, one round), with the bf16 result as their only output: tiles that
+    all lie inside, and ragged last rows and columns.  One step per sequence, so every
+    row is computed on its own; rows around the first tiles' edge and the whole last
+    row block, all columns, and the last columns by themselves."""
+    N = 16
+    say(f"[stack wide tiles] M={M} D={D}")
+    inp = make_stack_inputs(1, M, 1, D, N, 692410, device="cuda")
+    yK = ssm.ssm_stack_grad(inp["y0"], inp["W_in"], inp["W_x"], inp["A_log"], None, N, forward_only=True)["yK"]
+    torch.cuda.synchronize()
+    rows = [*range(4), *range(250, 262), *range(7676, M)]
+    y0 = to_np(inp["y0"])[rows]
+    ref, _ = ostack.stack_forward(y0, *([to_np(t) for t in inp[k]] for k in ("W_in", "W_x", "A_log")), N)
+    got, ref = to_np(yK)[rows] - y0, ref - y0
+    rep = {}
+    for name, r, c in [("all", slice(None), slice(None)), ("last column block", slice(None), slice(1280, D)),
+                       ("last 8 columns", slice(None), slice(D - 8, D)), ("last row", slice(-1, None), slice(None)),
+                       ("last corner", slice(-8, None), slice(D - 8, D))]:
+        check(f"yK - y0, {name}", got[r, :, c], ref[r, :, c], TOL_BF16, rep)
+    say("   rel-L2 max:", f"{max(rep.values()):.2e}")
+
+
 def test_stack_modes_differ_as_in_the_oracle():
     """The last layer's gradient is the same under both gradients (bit for bit on
     the GPU); below it, the GPU's difference between Prop. 3 and backpropagation
