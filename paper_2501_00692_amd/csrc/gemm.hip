@@ -1090,36 +1090,46 @@ constexpr int64_t kMaxWgs = (int64_t(1) << 23) - 1;
 // Output-tile width and reduction splits for the outputs R_q x Cc_q of one launch
 // (one or two products) with reduction Kr, from a simple time model: rounds of 256
 // workgroups x the time of one workgroup's share (per 32 steps at full load,
-// measured: 0.57 us for 128 columns, 0.80 for 192; 256 on the four-wave kernels:
-// `wide_us`, 0.84 for dW, 0.70 for dX from 1,024 reduction steps on; with fewer, the
-// filling of its stages and the store weigh more: priced as dW), plus the
-// HBM time of writing and re-reading the split partials (4 TB/s).  256-column
-// tiles (`wide`) for dW, and for dX when its epilogue is plain (no addend, and
-// either the fp32 result or its bf16 copy: the four-wave kernel's registers hold
-// no more).
+// measured: 0.57 us for 128 columns, 0.80 for 192, 0.84 for 256 with the dW form), plus
+// the HBM time of writing and re-reading the split partials (4 TB/s).  256-column
+// tiles for dW, and for dX when its epilogue is plain (no addend, and either the fp32
+// result or its bf16 copy: the four-wave kernel's registers hold no more).
+// Plain dX: a 256-column tile costs 0.76 us per 32 steps and 0.8 for the filling of its
+// stages and its store, and a last round of 192-column tiles that is part filled counts
+// 0.6 of a whole one and 0.4 of its part (two waves per SIMD: the fewer tiles, the faster
+// each).  With a flat 0.70 from 1,024 steps on (0.84 below), 256 was taken where its tiles
+// barely enter another round: 4,864 x 3,672 x 2,416 (285 against 380 tiles) 125 us, with
+// 192 columns 121; 51,397 x 2,168 x 64 118 and 110.  Over 110 shapes and every width and
+// split the choice is 1.2 % from the best measured (1.5 % with the flat prices).
 struct Plan {
     int bn;
     int splits;
 };
 
-Plan plan_gemm(int np, const int64_t* R, const int64_t* Cc, int64_t Kr, bool allow_split, bool wide, double wide_us) {
+enum class Form { dw, dx, dx_plain };
+
+Plan plan_gemm(int np, const int64_t* R, const int64_t* Cc, int64_t Kr, Form form) {
     Plan best{192, 1};
     double best_us = 1e300;
+    const bool plain = form == Form::dx_plain;
     const int bns[3] = {192, 128, 256};
-    const double step_us[3] = {0.80, 0.57, wide_us};
+    const double step_us[3] = {0.80, 0.57, plain ? 0.76 : 0.84};
+    const double tile_us[3] = {0.0, 0.0, plain ? 0.8 : 0.0};
+    const double part[3] = {plain ? 0.4 : 0.0, 0.0, 0.0};  // share of a last round priced by its part
     double out = 0.0;  // output elements of all products
     for (int q = 0; q < np; ++q) out += static_cast<double>(R[q]) * static_cast<double>(Cc[q]);
     for (int b = 0; b < 3; ++b) {
         const int bn = bns[b];
-        if (bn == 256 && !wide) continue;
+        if (bn == 256 && form == Form::dx) continue;
         int64_t tiles = 0;
         for (int q = 0; q < np; ++q) tiles += cdiv64(R[q], BM) * cdiv64(Cc[q], bn);
         const int64_t iters = (Kr + BK - 1) / BK;
-        for (int s = 1; s <= (allow_split ? 32 : 1); ++s) {
+        for (int s = 1; s <= 32; ++s) {
             if (s > 1 && iters / s < 8) break;
             const int64_t wgs = tiles * s;
-            const double rounds = static_cast<double>((wgs + kCUs - 1) / kCUs);
-            double us = rounds * step_us[b] * static_cast<double>((iters + s - 1) / s);
+            double rounds = static_cast<double>((wgs + kCUs - 1) / kCUs);
+            if (rounds > 1.0) rounds += part[b] * (static_cast<double>(wgs) / kCUs - rounds);
+            double us = rounds * (step_us[b] * static_cast<double>((iters + s - 1) / s) + tile_us[b]);
             if (s > 1) us += static_cast<double>(s) * out * 8.0 / 4e12 * 1e6;
             if (us < best_us * 0.999) {
                 best_us = us;
@@ -1129,8 +1139,8 @@ Plan plan_gemm(int np, const int64_t* R, const int64_t* Cc, int64_t Kr, bool all
     }
     return best;
 }
-Plan plan_gemm(int64_t R, int64_t Cc, int64_t Kr, bool allow_split, bool wide) {
-    return plan_gemm(1, &R, &Cc, Kr, allow_split, wide, Kr >= 1024 ? 0.70 : 0.84);
+Plan plan_dx(int64_t R, int64_t Cc, int64_t Kr, bool plain) {
+    return plan_gemm(1, &R, &Cc, Kr, plain ? Form::dx_plain : Form::dx);
 }
 
 // 256-column tiles run on the four-wave kernel with kStages4 stages.
@@ -1216,7 +1226,7 @@ size_t dw_workspace(int np, const DwProduct* d, int64_t M) {
         R[q] = d[q].K;
         Cc[q] = d[q].N;
     }
-    return split_workspace(plan_gemm(np, R, Cc, M, true, true, 0.84), np, R, Cc);
+    return split_workspace(plan_gemm(np, R, Cc, M, Form::dw), np, R, Cc);
 }
 
 hipError_t launch_dw(int np, const DwProduct* d, int64_t M, void* ws, hipStream_t s, const char* timer = nullptr) {
@@ -1225,7 +1235,7 @@ hipError_t launch_dw(int np, const DwProduct* d, int64_t M, void* ws, hipStream_
         R[q] = d[q].K;
         Cc[q] = d[q].N;
     }
-    const Plan pl = plan_gemm(np, R, Cc, M, true, true, 0.84);
+    const Plan pl = plan_gemm(np, R, Cc, M, Form::dw);
     const bool direct = pl.splits == 1;
     GemmArgs g[2];
     ReduceArgs fin[2];
@@ -1262,8 +1272,8 @@ size_t gemm_dw2_workspace(int64_t M, const DwProduct& a, const DwProduct& b) {
 
 size_t gemm_dx_workspace(int64_t M, int64_t K, int64_t N) {
     // either epilogue (the plan with 256-column tiles applies to plain ones)
-    const size_t a = split_workspace(plan_gemm(M, K, N, true, false), 1, &M, &K);
-    const size_t b = split_workspace(plan_gemm(M, K, N, true, true), 1, &M, &K);
+    const size_t a = split_workspace(plan_dx(M, K, N, false), 1, &M, &K);
+    const size_t b = split_workspace(plan_dx(M, K, N, true), 1, &M, &K);
     return a > b ? a : b;
 }
 
@@ -1286,7 +1296,7 @@ hipError_t launch_gemm_dx(int64_t M, int64_t K, int64_t N, const uint16_t* dZ, i
     if (ldx <= 0) ldx = K;
     if (ldadd <= 0) ldadd = K;
     // outputs with few tiles (narrow projections) split the reduction as dW does
-    const Plan pl = plan_gemm(M, K, N, true, add == nullptr && (out16 == nullptr || dX == nullptr));
+    const Plan pl = plan_dx(M, K, N, add == nullptr && (out16 == nullptr || dX == nullptr));
     const bool direct = pl.splits == 1;
     const GemmArgs g{M, K, N, dZ, lddz, W, ldw, direct ? dX : static_cast<float*>(ws), split_range(N, pl.splits),
                      direct ? 1 : 0, accum ? 1 : 0, add, out16, ld16, ldx, ldadd};
@@ -1308,13 +1318,13 @@ hipError_t launch_gemm_dx(int64_t M, int64_t K, int64_t N, const uint16_t* dZ, i
 // each, every one of them too small to fill the GPU (768 x 1536 x 1568: 54 -> 35 us;
 // 2048 x 4096 x 4128, not split before: 213 -> 164).
 size_t gemm_hilo_workspace(int64_t M, int64_t K, int64_t N) {
-    const Plan pl = plan_gemm(2 * M, K, N, true, true);
+    const Plan pl = plan_dx(2 * M, K, N, true);
     return static_cast<size_t>(pl.splits) * 2 * M * K * sizeof(float);
 }
 
 hipError_t launch_gemm_hilo(int64_t M, int64_t K, int64_t N, const uint16_t* hilo, const uint16_t* W, int64_t ldw, float* dst,
                             int64_t ldd, const float* add, int64_t ldadd, void* ws, hipStream_t s) {
-    const Plan pl = plan_gemm(2 * M, K, N, true, true);
+    const Plan pl = plan_dx(2 * M, K, N, true);
     GemmArgs g{2 * M, K, N, hilo, N, W, ldw, static_cast<float*>(ws), split_range(N, pl.splits), 0, 0, nullptr, nullptr, 0,
                K, 0};
     {
