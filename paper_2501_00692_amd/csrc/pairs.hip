@@ -62,7 +62,9 @@ template <typename TI, bool N16>
 __global__ __launch_bounds__(kPairLanes) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_pairs(
     const ScanProblem p, const float* dlv, const float* gv, float* mu, int64_t W) {
     constexpr int IB = kPairSteps, NS = kPairStates;
-    constexpr int PB = sizeof(TI) == 2 ? 4 : 2;  // steps t loaded ahead of their use
+    // steps t loaded ahead of their use: four where a step's C is four registers (bf16, 16
+    // states), two where it is eight (four there spilled 13 registers)
+    constexpr int PB = N16 && sizeof(TI) == 2 ? 4 : 2;
     using Bits = typename RawIn<TI, 1>::Bits;
     const int lane = threadIdx.x;
     const int64_t d = static_cast<int64_t>(blockIdx.y) * kPairLanes + lane;

@@ -70,8 +70,8 @@ def test_pairs_ragged(chunk, tbar):
 @pytest.mark.parametrize("N,bf16", [(16, False), (16, True), (11, False), (5, True)])
 @pytest.mark.parametrize("T,tbar", [(1, 0), (7, 3), (8, 8), (9, 1), (15, 7), (17, 8), (23, 9), (24, 16), (41, 12), (64, 0)])
 def test_pairs_step_blocks(T, tbar, N, bf16):
-    """The kernel takes 8 steps i and 8 states per wave and 4 (fp32: 2) steps t per
-    batch: sequences and windows around those sizes."""
+    """The kernel takes 8 steps i and 8 states per wave and 4 steps t per batch (bf16
+    with 16 states, else 2): sequences and windows around those sizes."""
     w = Workload("pairs_blocks", 2, T, 67, N, 67, 0, False, bf16, 692113, delta_scale=0.125)
     say(f"[pairs blocks] T={T} N={N} bf16={bf16} tbar={tbar}")
     inp = make_inputs(w, device="cuda")

@@ -89,3 +89,12 @@ def test_gemm_keeps_its_accumulators(kernels):
     assert len(got) >= 4
     for name, k in got:
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
+
+
+def test_pairs_hold_two_waves(kernels):
+    """The pair kernel's products and sums of 8 steps by 8 states: two waves per SIMD and
+    nothing in scratch, in all four forms."""
+    got = _pick(kernels, "7k_pairsI")
+    assert len(got) == 4
+    for name, k in got:
+        assert k[".vgpr_count"] <= 256 and k[".private_segment_fixed_size"] == 0, name
