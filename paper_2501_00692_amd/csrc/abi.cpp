@@ -1047,14 +1047,14 @@ ssm_status ssm_lm_head_grad(int64_t M, int64_t P, int64_t V, uint32_t flags, int
             HEAD_HIP(ssmk::launch_to_bf16(yb, u, mb * P, s), "ssm_lm_head_grad input");
         // logits [mb][V] = u Omega^T, the reduction over P: the dX form (3.88 ms at 32,768 x
         // 32,000 x 2,048; the weight-gradient form from a transposed u 4.04 and 0.12)
-        HEAD_HIP(ssmk::launch_gemm_dx(mb, V, P, u, P, om, P, logit, false, nullptr, nullptr, 0, gws, s, 0, 0,
+        HEAD_HIP(ssmk::launch_gemm_dx(mb, V, P, u, P, om, P, logit, false, nullptr, nullptr, 0, gws, s,
                                       "head_logits"),
                  "ssm_lm_head_grad logits");
         HEAD_HIP(ssmk::launch_head_xent(logit, V, targets + m0, loss + m0, G, V, mb, V, s),
                  "ssm_lm_head_grad loss");
         // dU [mb][P] = G Omega = G (Omega^T)^T: the dX form with the reduction over V
         HEAD_HIP(ssmk::launch_gemm_dx(mb, P, V, G, V, omt, V, norm ? du : dyb, false, nullptr, nullptr, 0, gws, s,
-                                      0, 0, "head_du"),
+                                      "head_du"),
                  "ssm_lm_head_grad dU");
         if (norm) HEAD_HIP(ssmk::launch_rms_bwd(yb, rinv, du, dyb, nullptr, mb, P, s, false), "ssm_lm_head_grad dy");
         if (domega)  // dOmega [V][P] (+)= G^T u, the blocks added in order

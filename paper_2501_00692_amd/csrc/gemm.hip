@@ -134,15 +134,13 @@ struct GemmArgs {
     int64_t lda;
     const uint16_t* B;    // TR: [Kr][Cc];                  else [Cc][Kr]
     int64_t ldb;
-    float* C;             // output [R][Cc] (ldc = Cc), or split partials
+    float* C;             // output [R][Cc], or split partials
     int64_t kper;         // reduction range per split (multiple of BK)
     int direct;           // write C (else the partial of the workgroup's split)
     int accum;            // C += result
-    const float* add;     // optional fp32 addend [R][Cc] (row stride ldadd)
+    const float* add;     // optional fp32 addend [R][Cc]
     uint16_t* out16;      // optional bf16 copy of the result
     int64_t ld16;
-    int64_t ldc;          // row stride of C when written directly (split partials: Cc)
-    int64_t ldadd;        // row stride of add
 };
 
 // One launch covers the output tiles of one product, or of two products with the
@@ -545,7 +543,7 @@ __global__ __launch_bounds__(512) void k_gemm(const GemmLaunch gl) {
     auto store = [&](auto Ft, auto Mt) __attribute__((always_inline)) {
         constexpr int M = decltype(Mt)::value;
         store_tile<(M & 1) != 0, (M & 2) != 0, (M & 4) != 0, (M & 8) != 0, decltype(Ft)::value>(
-            acc, dst, g.direct ? g.ldc : g.Cc, addp, g.ldadd, o16, g.ld16, g.R, g.Cc, r0 + wr, c0 + wc, lane);
+            acc, dst, g.Cc, addp, g.Cc, o16, g.ld16, g.R, g.Cc, r0 + wr, c0 + wc, lane);
     };
     auto by_mask = [&](auto Ft) __attribute__((always_inline)) {
         if constexpr (TR) {  // dW: C or C += (split partials are C)
@@ -765,12 +763,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 
     float* dst = g.C + (g.direct ? 0 : static_cast<int64_t>(split) * g.R * g.Cc);
-    const int64_t ldc = g.direct ? g.ldc : g.Cc;
     const bool accum = g.direct && g.accum;
     const bool full = r0 + BM <= g.R && c0 + BN <= g.Cc;
     auto store = [&](auto Ft, auto At) __attribute__((always_inline)) {
         store_tile<false, decltype(At)::value, true, false, decltype(Ft)::value>(
-            acc, dst, ldc, nullptr, 0, nullptr, 0, g.R, g.Cc, r0 + wr, c0 + wc, lane);
+            acc, dst, g.Cc, nullptr, 0, nullptr, 0, g.R, g.Cc, r0 + wr, c0 + wc, lane);
     };
     if (full) {
         if (accum) store(std::true_type{}, std::true_type{});
@@ -999,7 +996,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 
     float* dst = g.C + (g.direct ? 0 : static_cast<int64_t>(split) * g.R * g.Cc);
-    const int64_t ldc = g.direct ? g.ldc : g.Cc;
     if constexpr (EP == Ep::bf16) {
         if (FULL || (r0 + BM <= g.R && c0 + 256 <= g.Cc))
             store_tile<false, false, false, true, true>(acc, nullptr, 0, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0 + wr,
@@ -1007,11 +1003,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         else
             store_block<false, true>(acc, nullptr, 0, g.out16, g.ld16, g.R, g.Cc, r0, c0, wr, wc, lane);
     } else if constexpr (EP == Ep::accum) {
-        store_block<true, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
+        store_block<true, false>(acc, dst, g.Cc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
     } else if constexpr (FULL) {
-        store_tile<false, false, true, false, true>(acc, dst, ldc, nullptr, 0, nullptr, 0, g.R, g.Cc, r0 + wr, c0 + wc, lane);
+        store_tile<false, false, true, false, true>(acc, dst, g.Cc, nullptr, 0, nullptr, 0, g.R, g.Cc, r0 + wr, c0 + wc, lane);
     } else {
-        store_block<false, false>(acc, dst, ldc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
+        store_block<false, false>(acc, dst, g.Cc, nullptr, 0, g.R, g.Cc, r0, c0, wr, wc, lane);
     }
 }
 
@@ -1242,8 +1238,7 @@ hipError_t launch_dw(int np, const DwProduct* d, int64_t M, void* ws, hipStream_
     float* part = static_cast<float*>(ws);
     for (int q = 0; q < np; ++q) {
         g[q] = GemmArgs{d[q].K, d[q].N, M, d[q].X, d[q].ldx, d[q].dZ, d[q].lddz, direct ? d[q].dW : part,
-                        split_range(M, pl.splits), direct ? 1 : 0, d[q].accum ? 1 : 0, nullptr, nullptr, 0,
-                        d[q].N, 0};
+                        split_range(M, pl.splits), direct ? 1 : 0, d[q].accum ? 1 : 0, nullptr, nullptr, 0};
         fin[q] = ReduceArgs{0, 0, nullptr, d[q].dW, d[q].accum ? 1 : 0, nullptr, nullptr, 0, d[q].N, 0};
         if (!direct) part += static_cast<int64_t>(pl.splits) * d[q].K * d[q].N;
     }
@@ -1291,22 +1286,19 @@ hipError_t launch_gemm_dw2(int64_t M, const DwProduct& a, const DwProduct& b, vo
 
 hipError_t launch_gemm_dx(int64_t M, int64_t K, int64_t N, const uint16_t* dZ, int64_t lddz,
                           const uint16_t* W, int64_t ldw, float* dX, bool accum, const float* add,
-                          uint16_t* out16, int64_t ld16, void* ws, hipStream_t s, int64_t ldx, int64_t ldadd,
-                          const char* timer) {
-    if (ldx <= 0) ldx = K;
-    if (ldadd <= 0) ldadd = K;
+                          uint16_t* out16, int64_t ld16, void* ws, hipStream_t s, const char* timer) {
     // outputs with few tiles (narrow projections) split the reduction as dW does
     const Plan pl = plan_dx(M, K, N, add == nullptr && (out16 == nullptr || dX == nullptr));
     const bool direct = pl.splits == 1;
     const GemmArgs g{M, K, N, dZ, lddz, W, ldw, direct ? dX : static_cast<float*>(ws), split_range(N, pl.splits),
-                     direct ? 1 : 0, accum ? 1 : 0, add, out16, ld16, ldx, ldadd};
+                     direct ? 1 : 0, accum ? 1 : 0, add, out16, ld16};
     {
         SSMK_TIMED(timer ? timer : "gemm_dx", s);
         if (!launch_plan<false>(&g, 1, pl, s)) return hipErrorInvalidConfiguration;
     }
     if (!direct) {
         SSMK_TIMED("splitk_reduce", s);
-        const ReduceArgs fin{0, 0, nullptr, dX, accum ? 1 : 0, add, out16, ld16, ldx, ldadd};
+        const ReduceArgs fin{0, 0, nullptr, dX, accum ? 1 : 0, add, out16, ld16, K, K};
         launch_reduce(&g, &fin, 1, pl.splits, s);
     }
     return hipGetLastError();
@@ -1325,8 +1317,7 @@ size_t gemm_hilo_workspace(int64_t M, int64_t K, int64_t N) {
 hipError_t launch_gemm_hilo(int64_t M, int64_t K, int64_t N, const uint16_t* hilo, const uint16_t* W, int64_t ldw, float* dst,
                             int64_t ldd, const float* add, int64_t ldadd, void* ws, hipStream_t s) {
     const Plan pl = plan_dx(2 * M, K, N, true);
-    GemmArgs g{2 * M, K, N, hilo, N, W, ldw, static_cast<float*>(ws), split_range(N, pl.splits), 0, 0, nullptr, nullptr, 0,
-               K, 0};
+    GemmArgs g{2 * M, K, N, hilo, N, W, ldw, static_cast<float*>(ws), split_range(N, pl.splits), 0, 0, nullptr, nullptr, 0};
     {
         SSMK_TIMED("gemm_dwin_fix", s);
         if (!launch_plan<false>(&g, 1, pl, s)) return hipErrorInvalidConfiguration;

@@ -195,12 +195,11 @@ hipError_t launch_gemm_dw2(int64_t M, const DwProduct& a, const DwProduct& b, vo
 // be NULL when out16 is given (only the copy is written).  Narrow outputs split the
 // reduction: ws holds gemm_dx_workspace(M, K, N) bytes (none otherwise).
 size_t gemm_dx_workspace(int64_t M, int64_t K, int64_t N);
-// ldx and ldadd are the row strides of dX and of the addend (0: K); `timer` names
-// the launch in the per-kernel timing (default "gemm_dx").
+// `timer` names the launch in the per-kernel timing (default "gemm_dx").
 hipError_t launch_gemm_dx(int64_t M, int64_t K, int64_t N, const uint16_t* dZ, int64_t lddz,
                           const uint16_t* W, int64_t ldw, float* dX, bool accum, const float* add,
-                          uint16_t* out16, int64_t ld16, void* ws, hipStream_t s, int64_t ldx = 0,
-                          int64_t ldadd = 0, const char* timer = nullptr);
+                          uint16_t* out16, int64_t ld16, void* ws, hipStream_t s,
+                          const char* timer = nullptr);
 
 // dst[M][K] = add + (hi + lo) W^T for an fp32 [M][N] matrix held as two bf16 parts, hi
 // [M][N] followed by lo [M][N] (hilo), W [K][N] (ldw): the layer's reassociated

@@ -223,7 +223,7 @@ __device__ __forceinline__ float fin(uint32_t b, bool v) {
 // per step instead, next to their use, left every step waiting for a load: the
 // row's validity is wave-uniform, the compiler branched around the load, and the
 // branch's merge waited for all outstanding memory operations.
-template <typename TI, int S, bool N16>
+template <typename TI, int S>
 struct ShiftedC {
     static constexpr int CPL = S / 4;                    // states per lane
     static constexpr int BYTES = CPL * sizeof(TI);       // 4, 8 or 16
@@ -1465,7 +1465,7 @@ __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu
         RawIn<TI, SPL> nxs;  // raw inputs at the shifted positions (truncated mode)
         qin.template load<GATE, SPL>(vbi, (NCK - 1) * S, r, nxt);
         if constexpr (TRUNC) qis.template load<GATE, SPL>(D32, d32, (NCK - 1) * S, r, lims, dv, nxs);
-        using SC = ShiftedC<TI, S, N16>;
+        using SC = ShiftedC<TI, S>;
         typename std::conditional<N16, typename SC::Raw, typename SC::Few>::type nxc{}, curc{};
         auto load_c = [&](int qs) __attribute__((always_inline)) {  // shifted C rows of a segment (truncated mode)
             if constexpr (N16) nxc = SC::load(rsC, qs, lane);

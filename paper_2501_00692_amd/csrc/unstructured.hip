@@ -77,7 +77,6 @@ struct UnArgs {
     float* dC;
     float* dx;
     float* dh0;       // [b][16] or null (full mode)
-    float* h_last;    // [b][16] or null
     // workspace
     float* phi;       // [b][nc][16][16]
     float* hc;        // [b][nc][16]: local end state, then the carry into the chunk
@@ -484,7 +483,6 @@ hipError_t launch_unstructured_grad(const UnstructuredProblem& u, void* ws, hipS
     a.dC = u.dC;
     a.dx = u.dx;
     a.dh0 = u.dh0;
-    a.h_last = nullptr;
     auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
     char* w = static_cast<char*>(ws);
     a.phi = reinterpret_cast<float*>(w);
