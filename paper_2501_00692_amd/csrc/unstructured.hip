@@ -37,16 +37,17 @@
 // Lane layout of a wave: lane l = 16 q + i; the 16 x 16 matrices are held in the
 // MFMA output layout (component r of lane (q, i): row 4q + r, column i) and the
 // state vectors as such matrices with equal columns (component r: element 4q + r),
-// so that a step's product needs no data movement between lanes (mul_vals).
+// so that a step's product needs no data movement between lanes (mul_vals, mul_vec).
 // The passes over the steps are chains of dependent products.  What bounded them was
 // the latency of each step's loads, one step ahead, and of the lane exchanges of the
 // vector products; the loads now run 8 to 16 steps ahead (walk) and the vectors go
 // through MFMA.  At b = 8, T = 16,384, P = 64, tbar = 256: k_un_wsuf 187 -> 72 us,
-// k_un_wpre 96 -> 49, k_un_carry 82 -> 43, k_un_aggr 46 -> 39, k_un_madj 42 -> 25; what
+// k_un_wpre 96 -> 50, k_un_carry 82 -> 56, k_un_aggr 46 -> 43, k_un_madj 42 -> 28; what
 // is left there is the chain itself (a product is 64 cycles of MFMA latency and 128 of
 // the matrix pipe, so passes sharing a launch, or a SIMD, only take turns: measured
-// slower).  k_un_proj (1.16 GB, 254 us) and k_un_grad (2.1 GB, 460 us) run at the
-// rate of a plain copy, 4.6 TB/s.
+// slower; the vector products' tree of sums, mul_vec, is 12 more instructions a step).
+// k_un_proj (1.16 GB, 256 us) and k_un_grad (2.1 GB, 426 us) run at the rate of a plain
+// copy, 4.5 and 4.9 TB/s.
 #include "internal.h"
 
 namespace ssmk {
@@ -148,11 +149,20 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // lane's own X: the product needs no data movement and its result is again in
 // the output layout.  m4 holds the lane's operand values of M (M[i][4q + kb], a
 // float4 of row i; M[4q + kb][i] for M^T X, see vals_t), loaded ahead by the
-// caller; `add` is added to the product.  The four sums of four products are added as
-// a tree and `add` last: a chain of instructions from `add` on would be shorter by the
-// adds but round every step at add's magnitude (states and adjoints against 64 bits:
-// 12 and 8 % more error).
-__device__ __forceinline__ f4 mul_vals(const float4 m4, f4 X, f4 add = f4{0.f, 0.f, 0.f, 0.f}) {
+// caller.  Two chains of two instructions (each waits for the one before it).
+__device__ __forceinline__ f4 mul_vals(const float4 m4, f4 X) {
+    f4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+    a = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.x, X[0], a, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.z, X[2], b, 0, 0, 0);
+    a = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.y, X[1], a, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.w, X[3], b, 0, 0, 0);
+    return a + b;
+}
+// M x + add for a state or adjoint vector (all columns of X alike): the four sums of four
+// products are added as a tree and `add` last.  The chains of mul_vals started from `add`
+// are 12 adds a step fewer and round every partial sum at add's magnitude (states
+// and adjoints against 64 bits: 12 and 8 % more error).
+__device__ __forceinline__ f4 mul_vec(const float4 m4, f4 X, f4 add = f4{0.f, 0.f, 0.f, 0.f}) {
     const f4 z = {0.f, 0.f, 0.f, 0.f};
     const f4 p0 = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.x, X[0], z, 0, 0, 0);
     const f4 p1 = __builtin_amdgcn_mfma_f32_16x16x4f32(m4.y, X[1], z, 0, 0, 0);
@@ -230,7 +240,7 @@ __global__ __launch_bounds__(64) void k_un_aggr(const UnArgs a) {
                        ld4v(a.v + row * UN + 4 * q)};
         },
         [&](int64_t, const Rec& r) {
-            h = mul_vals(r.A, h, r.bx);  // h <- A_t h + B_t x_t
+            h = mul_vec(r.A, h, r.bx);  // h <- A_t h + B_t x_t
             phi = mul_vals(r.A, phi);    // Phi <- A_t Phi
             // the adjoint aggregate m += Phi_t^T v_t; lane (q, j): sum_r Phi[4q + r][j] v[4q + r]
             if (!a.trunc) m += dot4(phi, r.v);
@@ -264,7 +274,7 @@ __global__ __launch_bounds__(64) void k_un_carry(const UnArgs a) {
             },
             [&](int64_t k, const Rec& r) {
                 if (i == 0) st4v(a.mc + (c0 + nc - 1 - k) * UN + 4 * q, X);  // the carry from the right into the chunk
-                X = mul_vals(r.P, X, r.loc);
+                X = mul_vec(r.P, X, r.loc);
             });
         if (a.dh0 && i == 0) st4v(a.dh0 + bb * UN + 4 * q, X);
         return;
@@ -279,7 +289,7 @@ __global__ __launch_bounds__(64) void k_un_carry(const UnArgs a) {
         },
         [&](int64_t k, const Rec& r) {
             if (i == 0) st4v(a.hc + (c0 + k) * UN + 4 * q, X);  // the carry into the chunk
-            X = mul_vals(r.P, X, r.loc);
+            X = mul_vec(r.P, X, r.loc);
         });
 }
 
@@ -360,7 +370,7 @@ __global__ __launch_bounds__(64) void k_un_madj(const UnArgs a) {
     };
     walk<Rec>(
         s1 - s0, [&](int64_t j) { return Rec{vals_t(a.A + (re - j) * UN * UN, i, q), ld4v(a.v + (re - j) * UN + 4 * q)}; },
-        [&](int64_t, const Rec& r) { carry = mul_vals(r.A, r.v + carry); });
+        [&](int64_t, const Rec& r) { carry = mul_vec(r.A, r.v + carry); });
     if (i == 0) st4v(a.mc + (bb * a.nc + c) * UN + 4 * q, carry);
 }
 
@@ -394,7 +404,7 @@ __global__ __launch_bounds__(64 * kUnGradWaves) void k_un_grad(const UnArgs a) {
                 return Rec{*reinterpret_cast<const float4*>(a.A + row * UN * UN + i * UN + 4 * q), ld4v(a.bx + row * UN + 4 * q)};
             },
             [&](int64_t k, const Rec& r) {
-                h = mul_vals(r.A, h, r.v);
+                h = mul_vec(r.A, h, r.v);
                 if (i == 0) st4v(&shs[k + 1][4 * q], h);
             });
     } else if (wave == 1) {
@@ -410,7 +420,7 @@ __global__ __launch_bounds__(64 * kUnGradWaves) void k_un_grad(const UnArgs a) {
             [&](int64_t k, const Rec& r) {
                 const f4 mu = r.v + mun;
                 if (i == 0) st4v(&smu[n - 1 - k][4 * q], mu);
-                mun = mul_vals(r.A, mu);
+                mun = mul_vec(r.A, mu);
             });
     }
     __syncthreads();
