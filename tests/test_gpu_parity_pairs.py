@@ -78,6 +78,18 @@ def test_pairs_step_blocks(T, tbar, N, bf16):
     _compare(_pairs(inp, w, tbar, chunk=16), _oracle(inp, w, tbar), TOL_SCAN_BF16 if bf16 else TOL_F32, False)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("N", [1, 7, 8, 9])
+def test_pairs_state_halves(N, bf16):
+    """A wave has 8 of 16 states: up to 8 the second half has none and only zeros its
+    sums, with 9 it has one; steps past the end in the last block of 8."""
+    w = Workload("pairs_halves", 2, 45, 67, N, 67, 0, False, bf16, 692114, delta_scale=0.125)
+    say(f"[pairs halves] N={N} bf16={bf16}")
+    inp = make_inputs(w, device="cuda")
+    for tbar in (13, 0):
+        _compare(_pairs(inp, w, tbar, chunk=16), _oracle(inp, w, tbar), TOL_SCAN_BF16 if bf16 else TOL_F32, False)
+
+
 @pytest.mark.parametrize("w,tol", [(GATED, TOL_F32), (GATED16, TOL_SCAN_BF16)], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("tbar", [0, 24])
 def test_pairs_gate_softplus(w, tol, tbar):
