@@ -277,6 +277,16 @@ def workload_tag(w, chunk=0):
     return f"{w.name}-b{w.b}-T{w.T}-D{w.D}" + (f"-L{chunk}" if chunk else "")
 
 
+def chunk_in_use(ssm, w, chunk=0):
+    """The carry chunk a call runs with: the one asked for, or for 0 the default that the
+    library chooses by the sizes (the one whose workspace size is the same)."""
+    if chunk:
+        return chunk
+    size = [ssm.forward_workspace_size(ssm.SsmDesc(w.b, w.T, w.D, w.N, L, ssm.SSM_BF16 if w.bf16 else ssm.SSM_F32, 0))
+            for L in (0, 32, 64, 128)]
+    return (32, 64, 128)[size[1:].index(size[0])]
+
+
 def workload_text(w, modes):
     kind = ("one selective diagonal SSM layer with input projections and SiLU gate" if w.proj
             else "one selective diagonal SSM scan (per-layer gradients only, no projections)")
@@ -598,8 +608,8 @@ def main():
                                chunk=chunk)
             steps = 5 if wl.M >= 262144 else 10
             m, kt = _timed_kernels(st, steps, 2, ssm, torch)
-            entry = {"ms_per_step": m, "tokens_per_s": wl.M / (m * 1e-3), "tbar": tb, "chunk": chunk or "default",
-                     "kernels_ms": {k: v["avg_ms"] for k, v in kt.items()}}
+            entry = {"ms_per_step": m, "tokens_per_s": wl.M / (m * 1e-3), "tbar": tb,
+                     "chunk": chunk_in_use(ssm, wl, chunk), "kernels_ms": {k: v["avg_ms"] for k, v in kt.items()}}
             if kind == "pairs":
                 # the paper's unit of work: one (t, i) adjoint state over all D x N states
                 entry["vjp_pairs_per_s"] = wl.b * vjp_pairs(wl.T, tb) / (m * 1e-3)
@@ -664,7 +674,7 @@ def main():
         "config": {"workload": workload_text(w, list(MODES[w.name])),
                    "batch": w.b, "seq_len": w.T, "d_model": w.d_model if w.proj else None, "channels": w.D,
                    "dstate": w.N, "tbar": tbar, "inputs": "bf16" if w.bf16 else "fp32", "accumulate": "fp32",
-                   "chunk": args.chunk or "default (128)", "tokens_per_step": len(MODES[w.name]) * w.M},
+                   "chunk": chunk_in_use(ssm, w, args.chunk), "tokens_per_step": len(MODES[w.name]) * w.M},
         "modes": modes,
         "roofline": roofs[dom],
     }
