@@ -67,13 +67,13 @@ def layer_scan_bytes_per_token(D, N, s, dm):
 def layer_gemm_flops(M, D, N, dm):
     """Flops per launch of the layer's projection products, by timing name.  With
     d_model < D the input projection's gradient is reassociated: one weight-
-    gradient launch computes dW_x = x^T dZx and G = u^T [dx | dz | dZx], and two
-    small launches add (u^T dZx) W_x^T (its bf16 hi and lo parts) into dW_in.
+    gradient launch computes dW_x = x^T dZx and G = u^T [dx | dz | dZx], and one
+    small launch multiplies the bf16 hi and lo parts of u^T dZx by W_x^T for dW_in.
     Otherwise: dx_total = dx + dZx W_x^T (the dX launch), then dW_x and dW_in =
     u^T [dx_total | dz] in one launch."""
     nx = D + 2 * N
     if dm < D:
-        return {"gemm_dw": 2 * M * D * nx + 2 * M * dm * (3 * D + 2 * N), "gemm_dwin_fix": 2 * dm * nx * D}
+        return {"gemm_dw": 2 * M * D * nx + 2 * M * dm * (3 * D + 2 * N), "gemm_dwin_fix": 2 * 2 * dm * nx * D}
     return {"gemm_dw": 2 * M * D * nx + 2 * M * dm * 2 * D, "gemm_dx": 2 * M * nx * D}
 
 
