@@ -1045,7 +1045,7 @@ ssm_status ssm_lm_head_grad(int64_t M, int64_t P, int64_t V, uint32_t flags, int
             HEAD_HIP(ssmk::launch_rms_fwd(yb, u, rinv, mb, P, s), "ssm_lm_head_grad norm");
         else
             HEAD_HIP(ssmk::launch_to_bf16(yb, u, mb * P, s), "ssm_lm_head_grad input");
-        // logits [mb][V] = u Omega^T, the reduction over P: the dX form (3.88 ms at 32,768 x
+        // logits [mb][V] = u Omega^T, the reduction over P: the dX form (3.74 ms at 32,768 x
         // 32,000 x 2,048; the weight-gradient form from a transposed u 4.04 and 0.12)
         HEAD_HIP(ssmk::launch_gemm_dx(mb, V, P, u, P, om, P, logit, false, nullptr, nullptr, 0, gws, s,
                                       "head_logits"),

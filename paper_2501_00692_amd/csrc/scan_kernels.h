@@ -474,9 +474,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WANT_M && N1
         if constexpr (N16) {
             // Through LDS, so that each store of the wave is 1 KB of consecutive records.
             // Stored from the lanes' own registers, 16 bytes at every 64, the store path
-            // bound the kernel (slice workload, 8.6 GB of records: 5.3 -> 4.7 ms per call,
-            // 4.1 TB/s of its 19.2 GB where a plain copy reaches 4.7; T = 262,144, D = 3,072
-            // without gate and softplus: 3.68 -> 2.79 ms).
+            // bound the kernel (slice workload, 8.6 GB of records: 5.3 -> 4.7 ms per call with
+            // the decays next to their use; 4.4 with them in groups, which is 4.4 TB/s of its
+            // 19.2 GB where a plain copy reaches 4.7.  T = 262,144, D = 3,072 without gate and softplus:
+            // 3.68 -> 2.79 ms).
             wave_lds_sync();
 #pragma unroll
             for (int i = 0; i < 4; ++i) rows[lane][i] = make_float4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
@@ -1279,8 +1280,8 @@ struct QuadInPtr {
 //      taken out as it leaves), so it is carried at its own magnitude and never
 //      formed as the difference of two full-horizon adjoints.  Its value entering
 //      the chunk from the right, a_{e+1} mubar_{e+1}, is summed directly over the
-//      steps (e, e+tbar] when the window is shorter than the chunk; longer windows
-//      take M_c - P(e, e+tbar) a_{e+tbar+1} mu_{e+tbar+1}, with the full adjoint
+//      steps (e, e+tbar] when the window is shorter than p.direct (the chunk, or 128
+//      where the library chose a shorter chunk); longer windows take M_c - P(e, e+tbar) a_{e+tbar+1} mu_{e+tbar+1}, with the full adjoint
 //      carry at the shifted position (that of the chunk holding it, swept back to
 //      it); P(t, t+tbar) = 2^{cn W_t} with the window sum W_t = sum_{j=t+1}^{t+tbar}
 //      Delta_j kept in fp64.
