@@ -475,9 +475,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WANT_M && N1
             // Through LDS, so that each store of the wave is 1 KB of consecutive records.
             // Stored from the lanes' own registers, 16 bytes at every 64, the store path
             // bound the kernel (slice workload, 8.6 GB of records: 5.3 -> 4.7 ms per call with
-            // the decays next to their use; 4.4 with them in groups, which is 4.4 TB/s of its
-            // 19.2 GB where a plain copy reaches 4.7.  T = 262,144, D = 3,072 without gate and softplus:
-            // 3.68 -> 2.79 ms).
+            // the decays still next to their use; now 4.4 to 4.7 across boxes, up to 4.4 TB/s
+            // of its 19.2 GB where a plain copy reaches 4.7.  T = 262,144, D = 3,072 without gate
+            // and softplus: 3.68 -> 2.79 ms).
             wave_lds_sync();
 #pragma unroll
             for (int i = 0; i < 4; ++i) rows[lane][i] = make_float4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
