@@ -150,7 +150,8 @@ ssm_status ssm_adjoint_grad(const ssm_desc* desc, int32_t mode, int64_t tbar, co
  * GPU, held from the first call on that GPU until the process ends.  The call
  * allocates nothing.  It returns SSM_ERR_WORKSPACE, before anything is
  * enqueued, when the problem needs more scratch than that (exactly when
- * ssm_adjoint_grad_workspace_size reports more for the same arguments).  Every call on one GPU uses that GPU's single array: calls that
+ * ssm_adjoint_grad_workspace_size reports more for the same arguments).  Every call
+ * on one GPU uses that GPU's single array: calls that
  * can overlap on one GPU (different streams, or host threads) race and must be
  * serialised by the caller; calls on one stream are ordered.  No part of the
  * scratch needs to start at zero. */
